@@ -119,10 +119,13 @@ struct ntt_plan_s {
     std::mutex mu;
     bool ready = false;
     uint32_t W = 0;                 // words of Q
-    Tw* pow2 = nullptr;             // [L][kCrtMaxInWords]
-    Tw* inv = nullptr;              // [L]
-    uint64_t* M = nullptr;          // [L][W]
-    uint64_t* kQ = nullptr;         // [L + 1][W + 1]
+    bool all_wide = false;          // every prime has at least 47 bits
+    int8_t* dec = nullptr;          // digit matrix of the decomposition
+    int64_t* dec_off = nullptr;     // [kDecomposeSlices + 1][L][2]
+    nttk::DecomposePrime* dec_primes = nullptr;     // [L]
+    int8_t* rec = nullptr;          // digit matrix of the reconstruction (L <= kCrtMaxLimbs)
+    nttk::ReconstructPrime* rec_primes = nullptr;   // [L]
+    uint64_t* Q = nullptr;          // [W]
   } crt;
 
   // References: the creator's and one per batch that names the plan (plan_life.hpp).
@@ -166,7 +169,7 @@ struct ntt_plan_s {
     }
     void* ptrs[] = {d_q, d_mc, d_tw_fwd, d_tw_inv, d_ot_lo_fwd, d_ot_hi_fwd, d_ot_lo_inv, d_ot_hi_inv,
                     d_scale, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_q32, d_mu64,
-                    crt.pow2, crt.inv, crt.M, crt.kQ};
+                    crt.dec, crt.dec_off, crt.dec_primes, crt.rec, crt.rec_primes, crt.Q};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
   }
@@ -1491,30 +1494,38 @@ int32_t ntt_plan_word_bits(ntt_plan_t plan) {
 
 // ---------------------------------------------------------------- RNS <-> integers
 
-static constexpr uint32_t kCrtMaxLimbs = 64;   // reconstruction keeps L words per lane in LDS (32 KB)
+static constexpr uint32_t kCrtMaxLimbs = 64;   // reconstruction keeps L words per lane in registers
 
 // Build the conversion tables of a 64-bit plan and upload them (once).
 static ntt_status crt_prepare(ntt_plan_t plan) {
   std::lock_guard<std::mutex> lk(plan->crt.mu);
   if (plan->crt.ready) return NTT_OK;
   const nttc::CrtTables t = nttc::crt_tables(plan->primes);
-  std::vector<Tw> pow2(t.pow2.size()), inv(t.L);
+  std::vector<nttk::DecomposePrime> dp(t.L);
+  std::vector<nttk::ReconstructPrime> rp(t.L);
+  bool all_wide = true;
   for (uint32_t l = 0; l < t.L; ++l) {
     const uint64_t q = plan->primes[l];
-    for (uint32_t w = 0; w < nttc::kCrtMaxInWords; ++w) {
-      const uint64_t c = t.pow2[(size_t)l * nttc::kCrtMaxInWords + w];
-      pow2[(size_t)l * nttc::kCrtMaxInWords + w] = Tw{c, nttp::shoup_companion(c, q)};
-    }
-    inv[l] = Tw{t.inv[l], nttp::shoup_companion(t.inv[l], q)};
+    int s = 0;
+    while (s < 64 && (q >> s)) ++s;
+    dp[l] = {q, (uint32_t)(((nttp::u128)1 << (s + 31)) / q), s - 15};
+    rp[l] = {q, t.inv[l], nttp::shoup_companion(t.inv[l], q),
+             (uint64_t)(((nttp::u128)1 << 120) / ((nttp::u128)q << (62 - s)))};
+    all_wide = all_wide && s >= 47;
   }
+  const nttc::DecomposeMatrix dec = nttc::digit_matrix_decompose(plan->primes);
+  const std::vector<int8_t> rec = t.L <= kCrtMaxLimbs ? nttc::digit_matrix_reconstruct(t) : std::vector<int8_t>();
   DeviceGuard g(plan->device);
   if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
   hipError_t e;
-  if ((e = upload(&plan->crt.pow2, pow2)) != hipSuccess || (e = upload(&plan->crt.inv, inv)) != hipSuccess ||
-      (e = upload(&plan->crt.M, t.M)) != hipSuccess || (e = upload(&plan->crt.kQ, t.kQ)) != hipSuccess) {
+  if ((e = upload(&plan->crt.dec, dec.digits)) != hipSuccess ||
+      (e = upload(&plan->crt.dec_off, dec.offsets)) != hipSuccess ||
+      (e = upload(&plan->crt.dec_primes, dp)) != hipSuccess || (e = upload(&plan->crt.rec, rec)) != hipSuccess ||
+      (e = upload(&plan->crt.rec_primes, rp)) != hipSuccess || (e = upload(&plan->crt.Q, t.Q)) != hipSuccess) {
     if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of conversion tables failed");
     return hip_fail(e, "uploading conversion tables");
   }
+  plan->crt.all_wide = all_wide;
   plan->crt.W = t.W;
   plan->crt.ready = true;
   return NTT_OK;
@@ -1541,7 +1552,8 @@ ntt_status ntt_rns_decompose(ntt_plan_t plan, const uint64_t* d_words, uint32_t 
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
     const hipError_t e = nttk::launch_rns_decompose(d_words, n_words, d_res, n_polys, plan->logN, plan->L,
-                                                    plan->crt.pow2, nttc::kCrtMaxInWords, plan->d_q,
+                                                    plan->crt.dec, nttc::kDecomposeSlices, plan->crt.dec_primes,
+                                                    plan->crt.dec_off, plan->crt.all_wide,
                                                     static_cast<hipStream_t>(stream));
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_rns_decompose launch");
   } catch (const std::bad_alloc&) {
@@ -1563,7 +1575,7 @@ ntt_status ntt_crt_reconstruct(ntt_plan_t plan, const uint64_t* d_res, uint64_t*
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
     const hipError_t e = nttk::launch_crt_reconstruct(d_res, d_words, n_polys, plan->logN, plan->L, plan->crt.W,
-                                                      plan->crt.inv, plan->crt.M, plan->crt.kQ, plan->d_q,
+                                                      plan->crt.rec, plan->crt.rec_primes, plan->crt.Q,
                                                       static_cast<hipStream_t>(stream));
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_crt_reconstruct launch");
   } catch (const std::bad_alloc&) {

@@ -2,133 +2,310 @@
 // coefficient below Q = q_0 ... q_{L-1} is held as its L residues.  Integers are stored as
 // little-endian 64-bit words, word-major: word w of coefficient c of polynomial p sits at
 // (p*W + w)*N + c, so the lanes of a wave (consecutive coefficients) read consecutive words.
-// The tables come from crt_math.hpp (host).
+//
+// Both directions are products of a constant matrix with every coefficient's vector of base-256
+// digits (decomposition: the digits of 256^j mod q_l; reconstruction: the digits of Q / q_l, one
+// row per base-256 column of the result), so they run on the int8 matrix cores with exact int32
+// sums: at most 513 digit products of at most 2^14, below 2^24.  The tables come from
+// crt_math.hpp (host), laid out as the instruction's operands.
+//
+// A workgroup of four waves takes 256 coefficients, 64 per wave (two column groups of 32).  The
+// coefficients' digits stay in registers for the whole kernel, and the constant matrix streams
+// through LDS one 32-row tile at a time, loaded while the previous tile is multiplied, so each
+// workgroup reads the matrix (132 KB at 45 primes) once from L2.
 #include "kernels.hpp"
 #include "passes.hpp"
 
 namespace nttk {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+constexpr int kCvtThreads = 256;
+constexpr int kCvtGroups = 2;                        // column groups of 32 coefficients per wave
+constexpr int kCvtCoeffs = kCvtThreads / 64 * 32 * kCvtGroups;
+constexpr uint64_t kDigitBias = 0x8080808080808080ull;
 
 // b * w mod q in [0, 2q) for any b < 2^64, q < 2^62 (Shoup with the exact quotient).
 __device__ __forceinline__ uint64_t shoup_exact(uint64_t b, uint64_t w, uint64_t wb, uint64_t q) {
   return b * w - __umul64hi(b, wb) * q;
 }
 
-// residue l of coefficient c:  sum_w x_w * (2^(64 w) mod q_l)  mod q_l
-__global__ __launch_bounds__(256) void rns_decompose_kernel(const uint64_t* __restrict__ words, uint32_t W,
-                                                            uint64_t* __restrict__ res, uint64_t n_coeffs,
-                                                            uint32_t logN, uint32_t L,
-                                                            const Tw* __restrict__ pow2, uint32_t pow2_stride,
-                                                            const uint64_t* __restrict__ qs) {
-  const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t l = blockIdx.y;
-  if (j >= n_coeffs) return;
-  const uint64_t N = 1ull << logN;
-  const uint64_t p = j >> logN, c = j & (N - 1);
-  const uint64_t q = qs[l], q2 = q << 1;
-  const Tw* t = pow2 + (size_t)l * pow2_stride;
-  const uint64_t* x = words + p * W * N + c;
-  uint64_t acc = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    const Tw tw = t[w];
-    acc += shoup_exact(x[(size_t)w * N], tw.w, tw.wb, q);   // < 4q
-    acc = csub(acc, q2);                                     // < 2q
-  }
-  res[(p * L + l) * N + c] = csub(acc, q);
+__device__ __forceinline__ v4i digits16(uint64_t a, uint64_t b) {
+  return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)b, (int)(uint32_t)(b >> 32)};
 }
 
-constexpr int kCrtThreads = 64;
+// The values of the lanes (h, m) of the wave, h = lane / 32, seen from both halves.
+struct Halves {
+  uint32_t lo, hi;   // of lane (0, m) and of lane (1, m)
+};
+__device__ __forceinline__ Halves halves(uint32_t x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return Halves{r[0], r[1]};
+}
 
-// One coefficient per lane.  y_l = r_l * inv_l mod q_l goes to the lane's LDS column; then
-// x' = sum_l y_l M_l is formed word by word (product scanning: column w collects the low
-// words of y_l M_l[w] and the high words of y_l M_l[w-1] in a 192-bit accumulator) and
-// written out; finally the largest multiple kQ <= x' (k < L) is found by binary search from
-// the top words and subtracted, leaving x in [0, Q).
-__global__ __launch_bounds__(kCrtThreads) void crt_reconstruct_kernel(const uint64_t* __restrict__ res,
-                                                                      uint64_t* __restrict__ out, uint64_t n_coeffs,
-                                                                      uint32_t logN, uint32_t L, uint32_t W,
-                                                                      const Tw* __restrict__ inv,
-                                                                      const uint64_t* __restrict__ M,
-                                                                      const uint64_t* __restrict__ kQ,
-                                                                      const uint64_t* __restrict__ qs) {
-  extern __shared__ uint64_t ys[];   // [L][kCrtThreads]
-  const uint64_t j = (uint64_t)blockIdx.x * kCrtThreads + threadIdx.x;
-  if (j >= n_coeffs) return;         // no barrier below: each lane uses only its own column
-  const uint64_t N = 1ull << logN;
-  const uint64_t p = j >> logN, c = j & (N - 1);
-  for (uint32_t l = 0; l < L; ++l) {
-    const uint64_t q = qs[l];
-    const Tw t = inv[l];
-    ys[l * kCrtThreads + threadIdx.x] = csub(shoup_exact(res[(p * L + l) * N + c], t.w, t.wb, q), q);
-  }
-  uint64_t* o = out + p * W * N + c;
-  uint64_t c0 = 0, c1 = 0, c2 = 0;   // column w
-  uint64_t n0 = 0, n1 = 0, n2 = 0;   // column w + 1
-  for (uint32_t w = 0; w < W; ++w) {
-    for (uint32_t l = 0; l < L; ++l) {
-      const uint64_t y = ys[l * kCrtThreads + threadIdx.x], m = M[(size_t)l * W + w];
-      const uint64_t lo = y * m, hi = __umul64hi(y, m);
-      c0 += lo;
-      const uint64_t k0 = c0 < lo;
-      c1 += k0;
-      c2 += c1 < k0;
-      n0 += hi;
-      const uint64_t k1 = n0 < hi;
-      n1 += k1;
-      n2 += n1 < k1;
+// Streams the matrix tiles [T][S][64 lanes][16 digits] through two LDS buffers: `body(t, lds)` runs
+// with tile t's S slices in `lds`.  Every wave of the workgroup takes part in every tile.
+template <int KS, typename F>
+__device__ __forceinline__ void for_matrix_tiles(const v4i* __restrict__ frag, uint32_t stride, uint32_t T, uint32_t S,
+                                                 v4i (&lds)[2][KS * 64], F&& body) {
+  constexpr int PER = (KS * 64 + kCvtThreads - 1) / kCvtThreads;
+  const uint32_t tid = threadIdx.x, n = S * 64;
+  v4i next[PER];
+  auto fetch = [&](uint32_t t) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t e = tid + i * kCvtThreads;
+      if (e < n) next[i] = frag[(size_t)t * stride * 64 + e];
     }
-    o[(size_t)w * N] = c0;
-    // the next column takes the carries of this one
-    c0 = n0 + c1;
-    const uint64_t k0 = c0 < c1;
-    const uint64_t t1 = n1 + c2;
-    const uint64_t k1 = t1 < c2;
-    c1 = t1 + k0;
-    c2 = n2 + k1 + (c1 < k0);
-    n0 = n1 = n2 = 0;
-  }
-  const uint64_t top = c0;           // word W of x' (x' < L Q < 2^(64 W + 64))
-  // largest k with kQ[k] <= x', k in [0, L - 1]
-  uint32_t lo = 0, hi = L - 1;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) / 2;
-    const uint64_t* kq = kQ + (size_t)mid * (W + 1);
-    int cmp = top > kq[W] ? 1 : (top < kq[W] ? -1 : 0);
-    for (uint32_t w = W; cmp == 0 && w-- > 0;) {
-      const uint64_t xw = o[(size_t)w * N];
-      cmp = xw > kq[w] ? 1 : (xw < kq[w] ? -1 : 0);
+  };
+  auto put = [&](v4i* dst) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t e = tid + i * kCvtThreads;
+      if (e < n) dst[e] = next[i];
     }
-    if (cmp >= 0) lo = mid;
-    else hi = mid - 1;
-  }
-  const uint64_t* kq = kQ + (size_t)lo * (W + 1);
-  uint64_t borrow = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    const uint64_t xw = o[(size_t)w * N], s = kq[w];
-    const uint64_t d = xw - s;
-    const uint64_t b1 = xw < s;
-    const uint64_t d2 = d - borrow;
-    const uint64_t b2 = d < borrow;
-    o[(size_t)w * N] = d2;
-    borrow = b1 | b2;
+  };
+  fetch(0);
+  put(lds[0]);
+  __syncthreads();
+  for (uint32_t t = 0; t < T; ++t) {
+    if (t + 1 < T) fetch(t + 1);
+    body(t, lds[t & 1]);
+    if (t + 1 < T) put(lds[(t + 1) & 1]);   // last read before the previous barrier
+    __syncthreads();
   }
 }
+
+// One tile's products for both column groups: acc[g] = tile (32 rows) x digits of group g.
+template <int KS>
+__device__ __forceinline__ void tile_product(v16i (&acc)[kCvtGroups], const v4i* tile, const v4i (&b)[kCvtGroups][KS],
+                                             uint32_t S, uint32_t lane) {
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[g][r] = 0;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    if ((uint32_t)s < S) {
+      const v4i a = tile[s * 64 + lane];
+#pragma unroll
+      for (int g = 0; g < kCvtGroups; ++g) acc[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[g][s], acc[g], 0, 0, 0);
+    }
+  }
+}
+
+// c0 + 2^8 c1 + 2^16 c2 + 2^24 c3 + add over four int32 columns.
+template <int R>
+__device__ __forceinline__ int64_t columns4(const v16i& c, int64_t add) {
+  return add + (int64_t)c[R] + (int64_t)c[R + 1] * (1 << 8) + (int64_t)c[R + 2] * (1 << 16) +
+         (int64_t)c[R + 3] * (1 << 24);
+}
+
+// Residue l of an integer x: V = sum_j byte_j (256^j mod q_l), below 2^17 q_l, then one reduction.
+// The bytes enter as signed digits less 128, `offsets` adds the 128s back.  With s = bitlen(q_l),
+// t = floor(V / 2^(s-15)) < 2^32 and mu = floor(2^(s+31) / q_l) < 2^32, the estimate
+// floor(t mu / 2^46) of V / q_l falls short by less than 1 + 2^-13, so V - est q_l < 2 q_l.
+// 2 x 2^16 coefficients at 45 primes of 60 bits: 42 us (2.2 TB/s of words and residues; 132 matrix
+// instructions per 32 coefficients are 7 us of it), against 201 us for one exact Shoup product per
+// word and prime.  Bound by the loads of a wave's digits, which nothing of the same wave overlaps.
+template <int KS>
+__global__ __launch_bounds__(kCvtThreads, 2) void rns_decompose_kernel(
+    const uint64_t* __restrict__ words, uint32_t W, uint64_t* __restrict__ res, uint64_t n_coeffs, uint32_t logN,
+    uint32_t L, const v4i* __restrict__ frag, uint32_t stride, const DecomposePrime* __restrict__ primes,
+    const int64_t* __restrict__ offsets, uint32_t all_wide) {
+  __shared__ v4i lds[2][KS * 64];
+  const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = (W + 3) / 4;
+  const uint64_t N = 1ull << logN;
+  const uint64_t j0 = (uint64_t)blockIdx.x * kCvtCoeffs + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
+  v4i b[kCvtGroups][KS];
+  uint64_t* out[kCvtGroups];
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g) {
+    const uint64_t j = j0 + 32 * g < n_coeffs ? j0 + 32 * g : n_coeffs - 1;   // past the end: read, never stored
+    const uint64_t p = j >> logN, c = j & (N - 1);
+    const uint64_t* x = words + p * W * N + c;
+    out[g] = res + p * L * N + c;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const uint32_t w = 4 * s + 2 * h;
+      const uint64_t a0 = w < W ? x[(size_t)w * N] : 0, a1 = w + 1 < W ? x[(size_t)(w + 1) * N] : 0;
+      b[g][s] = digits16(a0 ^ kDigitBias, a1 ^ kDigitBias);
+    }
+  }
+  for_matrix_tiles<KS>(frag, stride, (L + 3) / 4, S, lds, [&](uint32_t t, const v4i* tile) {
+    const uint32_t l0 = 4 * t + 2 * h;
+    v16i acc[kCvtGroups];
+    tile_product<KS>(acc, tile, b, S, lane);
+    static_for<0, 2>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      const uint32_t l = l0 + u;
+      if (l < L) {
+        const DecomposePrime pr = primes[l];
+        const int64_t o0 = offsets[2 * l], o1 = offsets[2 * l + 1];
+#pragma unroll
+        for (int g = 0; g < kCvtGroups; ++g) {
+          const int64_t v0 = columns4<8 * u>(acc[g], o0), v1 = columns4<8 * u + 4>(acc[g], o1);
+          const uint64_t hi = (uint64_t)(v1 + (v0 >> 32));               // V >> 32 (V >= 0)
+          const uint64_t low = (hi << 32) | (uint32_t)v0;                // V mod 2^64
+          uint32_t q15;
+          if (all_wide) q15 = (uint32_t)(hi >> (pr.shift - 32));
+          else if (pr.shift >= 32) q15 = (uint32_t)(hi >> (pr.shift - 32));
+          else q15 = (uint32_t)(pr.shift >= 0 ? low >> pr.shift : low << -pr.shift);   // here V < 2^64
+          const uint32_t k = __umulhi(q15, pr.mu) >> 14;
+          const uint64_t r = csub(low - (uint64_t)k * pr.q, pr.q);
+          if (j0 + 32 * g < n_coeffs) out[g][(size_t)l * N] = r;
+        }
+      }
+    });
+  });
+}
+
+// x = sum_l y_l M_l - k Q with y_l = r_l inv_l mod q_l and k = floor(sum_l y_l / q_l).  k comes
+// from 2^56-scaled reciprocals: each term falls short by less than 1.25 units, so the sum plus 2^10
+// units gives k, or k + 1 when x lies within 2^-45 Q of Q; then x - Q < 0 shows in the sign of
+// the result and Q is added back.  Each lane half holds 16 consecutive base-256 columns of a
+// tile, carries them into four 32-bit words and passes its carry on (half 0 to half 1, half 1 to
+// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 39 us, against 576 us for
+// 64-bit products with a carry chain per product (93.6 M products of 64 x 64 bits at one wave per
+// SIMD) and a search for k; the same 132 matrix instructions as the decomposition.
+template <int KS>
+__global__ __launch_bounds__(kCvtThreads, 2) void crt_reconstruct_kernel(
+    const uint64_t* __restrict__ res, uint64_t* __restrict__ out, uint64_t n_coeffs, uint32_t logN, uint32_t L,
+    uint32_t W, const v4i* __restrict__ frag, const ReconstructPrime* __restrict__ primes,
+    const uint64_t* __restrict__ Q) {
+  __shared__ v4i lds[2][KS * 64];
+  const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = L / 4 + 1, T = W / 4 + 1;
+  const uint64_t N = 1ull << logN;
+  const uint64_t j0 = (uint64_t)blockIdx.x * kCvtCoeffs + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
+  v4i b[kCvtGroups][KS];
+  uint64_t* o[kCvtGroups];
+  const uint64_t* in[kCvtGroups];
+  uint64_t frac[kCvtGroups];
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g) {
+    const uint64_t j = j0 + 32 * g < n_coeffs ? j0 + 32 * g : n_coeffs - 1;   // past the end: read, never stored
+    const uint64_t p = j >> logN, c = j & (N - 1);
+    in[g] = res + p * L * N + c;
+    o[g] = out + p * W * N + c;
+    frac[g] = 0;
+  }
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    uint64_t y[kCvtGroups][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t l = 4 * s + 2 * h + u;
+#pragma unroll
+      for (int g = 0; g < kCvtGroups; ++g) y[g][u] = 0;
+      if (l < L) {
+        const ReconstructPrime pr = primes[l];
+        const uint32_t sh = __clzll(pr.q) - 2;
+#pragma unroll
+        for (int g = 0; g < kCvtGroups; ++g) {
+          y[g][u] = csub(shoup_exact(in[g][(size_t)l * N], pr.inv, pr.inv_b, pr.q), pr.q);
+          frac[g] += __umul64hi(y[g][u] << sh, pr.rec);
+        }
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < kCvtGroups; ++g)
+      b[g][s] = digits16((y[g][0] + kDigitBias) ^ kDigitBias, (y[g][1] + kDigitBias) ^ kDigitBias);
+  }
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g) {
+    const Halves f0 = halves((uint32_t)frac[g]), f1 = halves((uint32_t)(frac[g] >> 32));
+    const uint64_t f = make_u64(f0.lo, f1.lo) + make_u64(f0.hi, f1.hi) + 1024;
+    const int k = (int)(f >> 56);   // at most L <= 64: one digit
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      if ((uint32_t)s == L / 4 && (L % 4) / 2 == h) b[g][s][L % 2 ? 2 : 0] = k;
+  }
+  uint32_t carry[kCvtGroups] = {};   // out of the previous tile (signed)
+  uint32_t negative[kCvtGroups] = {};
+  for_matrix_tiles<KS>(frag, S, T, S, lds, [&](uint32_t t, const v4i* tile) {
+    v16i acc[kCvtGroups];
+    tile_product<KS>(acc, tile, b, S, lane);
+#pragma unroll
+    for (int g = 0; g < kCvtGroups; ++g) {
+      const int64_t t0 = columns4<0>(acc[g], h ? 0 : (int32_t)carry[g]);
+      const int64_t t1 = columns4<4>(acc[g], t0 >> 32);
+      const int64_t t2 = columns4<8>(acc[g], t1 >> 32);
+      const int64_t t3 = columns4<12>(acc[g], t2 >> 32);
+      int32_t over = (int32_t)(t3 >> 32);
+      const uint64_t lo = make_u64((uint32_t)t0, (uint32_t)t1), hi = make_u64((uint32_t)t2, (uint32_t)t3);
+      // half 1 takes half 0's carry: a sign-extended sum over both words and `over`
+      const Halves below = halves((uint32_t)over);   // outside the conditional: both halves take part
+      const int64_t cin = h ? (int32_t)below.lo : 0, sx = cin >> 63;
+      const uint64_t lo2 = lo + (uint64_t)cin, c0 = lo2 < lo;
+      const uint64_t hi1 = hi + (uint64_t)sx, hi2 = hi1 + c0;
+      over += (int32_t)sx + (int32_t)(hi1 < hi) + (int32_t)(hi2 < c0);
+      carry[g] = halves((uint32_t)over).hi;
+      negative[g] = halves((uint32_t)(hi2 >> 32)).hi >> 31;
+      const uint32_t w = 4 * t + 2 * h;
+      if (j0 + 32 * g < n_coeffs) {
+        if (w < W) o[g][(size_t)w * N] = lo2;
+        if (w + 1 < W) o[g][(size_t)(w + 1) * N] = hi2;
+      }
+    }
+  });
+  // x - Q came out for a lane of the wave: add Q back to the stored words, one lane per coefficient
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g) {
+    const bool fix = negative[g] && j0 + 32 * g < n_coeffs;
+    if (__any(fix)) {
+      __threadfence_block();   // the words that the other half's lanes stored
+      if (fix && h == 0) {
+        uint64_t c = 0;
+        for (uint32_t w = 0; w < W; ++w) {
+          const uint64_t a = o[g][(size_t)w * N], s = a + Q[w], r = s + c;
+          c = (uint64_t)(s < a) | (uint64_t)(r < s);
+          o[g][(size_t)w * N] = r;
+        }
+      }
+    }
+  }
+}
+
+// Slices of a launch rounded up to a built kernel: KS slices of digits stay in registers (8 VGPRs
+// each), so a short chain does not pay for a long one's registers.
+#define NTTK_CVT_CASES(X) X(2) X(4) X(8) X(12) X(17)
+
+static uint32_t cvt_blocks(uint64_t n) { return (uint32_t)((n + kCvtCoeffs - 1) / kCvtCoeffs); }
 
 hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res, uint32_t n_polys, uint32_t logN,
-                                uint32_t L, const Tw* pow2, uint32_t pow2_stride, const uint64_t* qs, hipStream_t st) {
+                                uint32_t L, const void* frag, uint32_t frag_slices, const DecomposePrime* primes,
+                                const int64_t* offsets, bool all_wide, hipStream_t st) {
   const uint64_t n = (uint64_t)n_polys << logN;
-  const dim3 grid((uint32_t)((n + 255) / 256), L);
-  hipLaunchKernelGGL(rns_decompose_kernel, grid, dim3(256), 0, st, words, W, res, n, logN, L, pow2, pow2_stride, qs);
-  return hipGetLastError();
+  const uint32_t S = (W + 3) / 4;
+  if (W == 0 || S > frag_slices) return hipErrorInvalidValue;
+#define X(KS)                                                                                                      \
+  if (S <= KS) {                                                                                                   \
+    hipLaunchKernelGGL(rns_decompose_kernel<KS>, dim3(cvt_blocks(n)), dim3(kCvtThreads), 0, st, words, W, res, n,  \
+                       logN, L, static_cast<const v4i*>(frag), frag_slices, primes, offsets + (size_t)S * L * 2,   \
+                       (uint32_t)all_wide);                                                                        \
+    return hipGetLastError();                                                                                      \
+  }
+  NTTK_CVT_CASES(X)
+#undef X
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_crt_reconstruct(const uint64_t* res, uint64_t* out, uint32_t n_polys, uint32_t logN, uint32_t L,
-                                  uint32_t W, const Tw* inv, const uint64_t* M, const uint64_t* kQ, const uint64_t* qs,
+                                  uint32_t W, const void* frag, const ReconstructPrime* primes, const uint64_t* Q,
                                   hipStream_t st) {
   const uint64_t n = (uint64_t)n_polys << logN;
-  const size_t lds = (size_t)L * kCrtThreads * sizeof(uint64_t);
-  hipLaunchKernelGGL(crt_reconstruct_kernel, dim3((uint32_t)((n + kCrtThreads - 1) / kCrtThreads)),
-                     dim3(kCrtThreads), lds, st, res, out, n, logN, L, W, inv, M, kQ, qs);
-  return hipGetLastError();
+  const uint32_t S = L / 4 + 1;
+  if (L > 64) return hipErrorInvalidValue;   // k must fit one digit
+#define X(KS)                                                                                                       \
+  if (S <= KS) {                                                                                                    \
+    hipLaunchKernelGGL(crt_reconstruct_kernel<KS>, dim3(cvt_blocks(n)), dim3(kCvtThreads), 0, st, res, out, n, logN, \
+                       L, W, static_cast<const v4i*>(frag), primes, Q);                                             \
+    return hipGetLastError();                                                                                       \
+  }
+  NTTK_CVT_CASES(X)
+#undef X
+  return hipErrorInvalidValue;
 }
 
 }  // namespace nttk

@@ -8,7 +8,10 @@
 //   M[l]       = Q / q_l, W words
 //   kQ[k]      = k * Q, W + 1 words, k = 0 .. L
 // Reconstruction forms x' = sum_l y_l M_l with y_l = r_l inv[l] mod q_l (so x' < L Q and
-// x' = x mod Q), finds the largest k with kQ <= x' and subtracts it.
+// x' = x mod Q) and subtracts the multiple k Q, k = floor(x' / Q).
+//
+// Both conversions run as products with a constant matrix of base-256 digits (digit_matrix_*
+// below), which the kernels take as int8 matrix-instruction operands.
 #pragma once
 #include <cstdint>
 #include <vector>
@@ -96,6 +99,93 @@ inline CrtTables crt_tables(const std::vector<uint64_t>& primes) {
     for (uint32_t w = 0; w < t.W + 1 && w < kq.size(); ++w) t.kQ[(size_t)k * (t.W + 1) + w] = kq[w];
   }
   return t;
+}
+
+// ------------------------------------------------------------------- digit matrices
+//
+// A matrix instruction multiplies a 32 x 32 tile of int8 digits (32 rows of the constant matrix,
+// a K slice of 32 digits) with 32 digits of 32 coefficients.  Lane (h, m) = (lane / 32, lane % 32)
+// of a wave holds 16 digits of the K slice: slots 2h and 2h + 1 of 8 digits each, where slot z
+// of slice s is limb (or word) 4 s + z.  The result of row m lands in lane half (m / 4) % 2,
+// register (m % 4) + 4 (m / 8); rows are assigned so that half h of the result holds 16
+// consecutive entries of the product.
+constexpr uint32_t kDigitTile = 64 * 16;   // bytes of one operand tile
+constexpr uint32_t tile_row(uint32_t m) { return 16 * ((m >> 2) & 1) + (m & 3) + 4 * (m >> 3); }
+
+// Base-256 digits of an integer in [-128, 127], one digit longer than its bytes; with `negate`
+// the digits of its negative (those of the integer then lie in [-127, 128]).
+inline std::vector<int8_t> signed_digits(const uint64_t* a, size_t words, bool negate) {
+  std::vector<int8_t> d(8 * words + 1);
+  int carry = 0;
+  for (size_t i = 0; i < d.size(); ++i) {
+    int v = (i < 8 * words ? (int)((a[i / 8] >> (8 * (i % 8))) & 255) : 0) + carry;
+    carry = v > (negate ? 128 : 127);
+    if (carry) v -= 256;
+    d[i] = (int8_t)(negate ? -v : v);
+  }
+  return d;
+}
+
+// Reconstruction: row b of the product is the base-256 column b of sum_l y_l M_l - k Q, where
+// limb l's slot holds the digits of y_l and slot L the digit k.  [tiles][slices] operand tiles.
+inline uint32_t reconstruct_tiles(uint32_t W) { return W / 4 + 1; }        // 32 columns each, sign included
+inline uint32_t reconstruct_slices(uint32_t L) { return L / 4 + 1; }       // L limbs and k
+inline std::vector<int8_t> digit_matrix_reconstruct(const CrtTables& t) {
+  const uint32_t T = reconstruct_tiles(t.W), S = reconstruct_slices(t.L);
+  std::vector<int8_t> f((size_t)T * S * kDigitTile, 0);
+  for (uint32_t l = 0; l <= t.L; ++l) {
+    const std::vector<int8_t> d = l < t.L ? signed_digits(&t.M[(size_t)l * t.W], t.W, false)
+                                          : signed_digits(t.Q.data(), t.W, true);
+    for (uint32_t tile = 0; tile < T; ++tile)
+      for (uint32_t m = 0; m < 32; ++m)
+        for (uint32_t i = 0; i < (l < t.L ? 8u : 1u); ++i) {
+          const int64_t at = (int64_t)32 * tile + tile_row(m) - i;   // column b takes digit b - i of M_l
+          if (at < 0 || at >= (int64_t)d.size()) continue;
+          const uint32_t lane = 32 * ((l % 4) / 2) + m;
+          f[((size_t)tile * S + l / 4) * kDigitTile + lane * 16 + 8 * (l % 2) + i] = d[(size_t)at];
+        }
+  }
+  return f;
+}
+
+// Decomposition: entry (l, i) of the product is sum_j u_j d_{j,i}, with d_{j,.} the digits of
+// 256^j mod q_l and u_j the integer's bytes less 128.  `offsets` adds the 128s back: for an integer
+// of s slices (32 s bytes), [s][l][z] is 128 sum_j d_{j,i} over i = 4 z .. 4 z + 3, weighted by
+// 256^(i mod 4).
+constexpr uint32_t kDecomposeSlices = kCrtMaxInWords / 4;
+struct DecomposeMatrix {
+  std::vector<int8_t> digits;      // [ceil(L / 4)][kDecomposeSlices] operand tiles
+  std::vector<int64_t> offsets;    // [kDecomposeSlices + 1][L][2]
+};
+inline DecomposeMatrix digit_matrix_decompose(const std::vector<uint64_t>& primes) {
+  const uint32_t L = (uint32_t)primes.size(), T = (L + 3) / 4, S = kDecomposeSlices;
+  constexpr uint64_t kBias = 0x8080808080808080ull;
+  DecomposeMatrix r;
+  r.digits.assign((size_t)T * S * kDigitTile, 0);
+  r.offsets.assign((size_t)(S + 1) * L * 2, 0);
+  uint32_t row_of[32];   // operand row of each entry of a tile
+  for (uint32_t m = 0; m < 32; ++m) row_of[tile_row(m)] = m;
+  for (uint32_t l = 0; l < L; ++l) {
+    const uint64_t q = primes[l];
+    const uint64_t b = 256 % q, bb = (uint64_t)(((u128)b << 64) / q);   // Shoup's product by 256
+    uint64_t c = 1 % q;
+    int64_t acc[2] = {0, 0};
+    for (uint32_t j = 0; j < 8 * kCrtMaxInWords; ++j) {
+      const uint32_t w = j / 8;
+      const uint64_t d = (c + kBias) ^ kBias;   // c < 2^62: eight signed digits hold it
+      int8_t* tile = &r.digits[((size_t)(l / 4) * S + w / 4) * kDigitTile];
+      for (uint32_t i = 0; i < 8; ++i) {
+        const int8_t di = (int8_t)(d >> (8 * i));
+        tile[(32 * ((w % 4) / 2) + row_of[8 * (l % 4) + i]) * 16 + 8 * (w % 2) + j % 8] = di;
+        acc[i / 4] += (int64_t)di * 128 * ((int64_t)1 << (8 * (i % 4)));
+      }
+      c = c * b - (uint64_t)(((u128)c * bb) >> 64) * q;
+      if (c >= q) c -= q;
+      if (j % 32 == 31)
+        for (int z = 0; z < 2; ++z) r.offsets[((size_t)(j / 32 + 1) * L + l) * 2 + z] = acc[z];
+    }
+  }
+  return r;
 }
 
 }  // namespace nttc

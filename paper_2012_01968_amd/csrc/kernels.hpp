@@ -51,11 +51,23 @@ hipError_t launch_transform32(uint32_t* data, const void* tw, const void* scale,
 hipError_t launch_pointwise32(const uint32_t* A, const uint32_t* B, uint32_t* C, const uint32_t* qs,
                               const uint64_t* mus, uint64_t n, uint32_t logN, uint32_t L, hipStream_t st);
 
-// RNS <-> integer conversion (crt.hip): integers as [n_polys][W][N] little-endian words.
+// RNS <-> integer conversion (crt.hip): integers as [n_polys][W][N] little-endian words.  `frag`
+// holds the digit matrices of crt_math.hpp.
+struct DecomposePrime {
+  uint64_t q;
+  uint32_t mu;      // floor(2^(s+31) / q), s = bitlen(q)
+  int32_t shift;    // s - 15
+};
+struct ReconstructPrime {
+  uint64_t q, inv, inv_b;   // (Q/q)^-1 mod q and its Shoup companion
+  uint64_t rec;             // floor(2^120 / (q << (62 - s)))
+};
+// `all_wide`: every prime has at least 47 bits (V >> (s - 15) comes from the high words alone).
 hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res, uint32_t n_polys, uint32_t logN,
-                                uint32_t L, const Tw* pow2, uint32_t pow2_stride, const uint64_t* qs, hipStream_t st);
+                                uint32_t L, const void* frag, uint32_t frag_slices, const DecomposePrime* primes,
+                                const int64_t* offsets, bool all_wide, hipStream_t st);
 hipError_t launch_crt_reconstruct(const uint64_t* res, uint64_t* out, uint32_t n_polys, uint32_t logN, uint32_t L,
-                                  uint32_t W, const Tw* inv, const uint64_t* M, const uint64_t* kQ, const uint64_t* qs,
+                                  uint32_t W, const void* frag, const ReconstructPrime* primes, const uint64_t* Q,
                                   hipStream_t st);
 
 // In-place bit-reversal permutation of every vector described by `a` (slot i <-> slot

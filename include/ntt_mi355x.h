@@ -222,15 +222,15 @@ ntt_status ntt_pointwise_mul(ntt_plan_t plan, const uint64_t* d_a, const uint64_
 
 /* Negacyclic product in Z_q[X]/(X^N+1) per vector (Section III-A):
  * c = iNTT(NTT(a) * NTT(b)).  Inputs and output are natural-order coefficients;
- * d_a and d_b are left unchanged; d_c may alias d_a but not d_b.  NTT(b) goes to a
- * plan-owned scratch buffer of n_polys*L*N*8 bytes, one per stream, grown on demand (the
- * growth waits for the stream's previous product). */
+ * d_a and d_b are left unchanged; d_c may alias d_a but not d_b.  b's (partial) transform
+ * goes to a plan-owned scratch buffer of n_polys*L*N*8 bytes, one per stream, grown on demand
+ * (the growth waits for the stream's previous product); single-pass sizes need none. */
 ntt_status ntt_polymul_negacyclic(ntt_plan_t plan, const uint64_t* d_a, const uint64_t* d_b, uint64_t* d_c,
                                   uint32_t n_polys, void* stream);
 
 /* The same product for callers that cannot allocate device memory (code under graph
  * capture, tight serving loops, hosts that forbid hipMalloc): identical arguments, result
- * and launches as ntt_polymul_negacyclic, but NTT(b) goes to one fixed 64 MiB device array
+ * and launches as ntt_polymul_negacyclic, but b's transform goes to one fixed 64 MiB device array
  * that the library holds on every device it runs on until the process ends, so the call
  * allocates nothing.  n_polys*L*N must not exceed ntt_polymul_noalloc_max_words() (2^23
  * residues), else NTT_ERR_ARG and nothing is enqueued; larger batches go in several calls.

@@ -21,13 +21,13 @@ SOURCES = ["kernels_fwd_fast.hip", "kernels_inv_fast.hip", "kernels_fwd_wide.hip
            "fused_fwd.hip", "fused_inv.hip", "kernels.hip", "permute.hip", "stages.hip", "kernels32.hip", "crt.hip",
            "calib.hip", "capi.cpp"]
 # (object name, source, defines): the row-pass instances, one unit per direction (forward,
-# inverse, key product), arithmetic policy and range of row lengths
+# inverse, key product, two-operand product), arithmetic policy and range of row lengths
 ROW_RANGES = ((1, 7), (8, 10), (11, 13))
 UNITS = [(os.path.splitext(src)[0], src, []) for src in SOURCES] + [
     (f"rows_{d}_{'fast' if fast else 'wide'}_{lo}_{hi}", "kernels_rows.hip",
      [f"-DNTTK_ROWS_DIR={d}", f"-DNTTK_ROWS_FAST={'true' if fast else 'false'}", f"-DNTTK_ROWS_LO={lo}",
       f"-DNTTK_ROWS_HI={hi}"])
-    for d in (0, 1, 2) for fast in (1, 0) for lo, hi in ROW_RANGES]
+    for d in (0, 1, 2, 3) for fast in (1, 0) for lo, hi in ROW_RANGES]
 ARCH = os.environ.get("NTT_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -72,7 +72,7 @@ def _compile(unit) -> str:
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     # the longest units first, at most one compiler per CPU (each takes a few GB)
-    order = sorted(UNITS, key=lambda u: (u[1] != "kernels_rows.hip", -int(u[2][3].split("=")[1]) if u[2] else 0))
+    order = sorted(UNITS, key=lambda u: (u[1] != "kernels_rows.hip", u[2] and u[2][0] < "-DNTTK_ROWS_DIR=2", u[2][2:] if u[2] else []))
     with ThreadPoolExecutor(max(1, min(len(order), os.cpu_count() or 1))) as ex:
         objs = list(ex.map(_compile, order))
     tmp = LIB + f".tmp{os.getpid()}"

@@ -606,41 +606,39 @@ static ntt_status check_product(ntt_plan_t plan, const uint64_t* d_a, const uint
   return NTT_OK;
 }
 
-// The launches of c = a * b with NTT(b) placed in `tmp` (n_polys*L*N words of device memory
-// that nothing else uses until they complete).  Split plans: NTT(b) into tmp (first pass out
-// of place), a's forward column pass out of place into c, the row passes with the product by
-// NTT(b) in one launch, and the inverse column pass; a single-pass size does the whole
-// product in that launch.  Fused-path plans: copies, both transforms, the element-wise
-// product and the inverse as separate launches.  Allocates nothing.
+// Whether a product needs scratch of the operands' size: a single-pass split plan reads both
+// operands, multiplies and writes c in one launch.
+static bool product_needs_scratch(ntt_plan_t plan) { return plan->kernel_path != NTT_PATH_SPLIT || plan->logN1 != 0; }
+
+// The launches of c = a * b with b's transform placed in `tmp` (n_polys*L*N words of device memory
+// that nothing else uses until they complete).  Split plans: the forward column passes of both
+// operands in one launch, out of place (a into c, b into tmp), the row passes of both with the
+// product in one launch, and the inverse column pass; a single-pass size does the whole
+// product in the row launch and leaves tmp alone.  Fused-path plans: copies, both transforms,
+// the element-wise product and the inverse as separate launches.  Allocates nothing.
 static hipError_t polymul_enqueue(ntt_plan_t plan, const uint64_t* d_a, const uint64_t* d_b, uint64_t* d_c,
                                   uint32_t n_polys, uint64_t* tmp, hipStream_t st) {
   hipError_t e;
   const int ot = plan->active_ot();
   if (plan->kernel_path == NTT_PATH_SPLIT) {
-    PassArgs fb = plan->args(tmp, n_polys, false);
-    PassArgs fa = plan->args(d_c, n_polys, false);
-    const PassArgs ia = plan->args(d_c, n_polys, true);
-    fb.src = d_b;
-    fa.src = d_a;
-    fa.key = tmp;
+    PassArgs rows = plan->args(d_c, n_polys, false);
+    const PassArgs inv = plan->args(d_c, n_polys, true);
     if (plan->logN1) {
-      PassArgs fa_col = fa;
-      fa_col.key = nullptr;
-      fa.src = nullptr;   // the row launch reads c, which the column pass wrote
-      PassArgs fb_row = fb;
-      fb_row.src = nullptr;
-      if ((e = nttk::launch_forward_pass(fb, ot, 0, st)) != hipSuccess ||
-          (e = nttk::launch_forward_pass(fb_row, ot, 1, st)) != hipSuccess ||
-          (e = nttk::launch_forward_pass(fa_col, ot, 0, st)) != hipSuccess ||
-          (e = nttk::launch_mul_rows(fa, ia, ot, st)) != hipSuccess ||
-          (e = nttk::launch_inverse_pass(ia, ot, 1, st)) != hipSuccess)
+      PassArgs cols = rows;
+      cols.src = d_a;
+      cols.data2 = tmp;
+      cols.src2 = d_b;
+      cols.n_vec *= 2;
+      cols.P *= 2;
+      rows.key = tmp;
+      if ((e = nttk::launch_forward_pass(cols, ot, 0, st)) != hipSuccess ||
+          (e = nttk::launch_mul_rows(rows, inv, ot, st)) != hipSuccess)
         return e;
-      return hipSuccess;
+      return nttk::launch_inverse_pass(inv, ot, 1, st);
     }
-    if ((e = nttk::launch_forward_pass(fb, ot, 0, st)) != hipSuccess ||
-        (e = nttk::launch_mul_rows(fa, ia, ot, st)) != hipSuccess)
-      return e;
-    return hipSuccess;
+    rows.src = d_a;
+    rows.key = d_b;
+    return nttk::launch_mul_rows(rows, inv, ot, st);
   }
   const size_t bytes = (size_t)n_polys * plan->L * plan->N * sizeof(uint64_t);
   if (d_c != d_a && (e = hipMemcpyAsync(d_c, d_a, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess) return e;
@@ -1155,10 +1153,13 @@ ntt_status ntt_polymul_negacyclic(ntt_plan_t plan, const uint64_t* d_a, const ui
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t bytes = (size_t)n_polys * plan->L * plan->N * sizeof(uint64_t);
-
+    hipError_t e;
+    if (!product_needs_scratch(plan)) {
+      e = polymul_enqueue(plan, d_a, d_b, d_c, n_polys, nullptr, st);
+      return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_polymul_negacyclic launch");
+    }
     ntt_plan_s::StreamScratch* sc = plan->scratch_for(st);
     std::lock_guard<std::mutex> lk(sc->mu);
-    hipError_t e;
     if (!sc->ev && (e = hipEventCreateWithFlags(&sc->ev, hipEventDisableTiming)) != hipSuccess) {
       sc->ev = nullptr;
       return hip_fail(e, "hipEventCreate");

@@ -3,7 +3,7 @@
 
 namespace nttk {
 // row passes: instantiated in kernels_rows.hip
-#define X(LM) NTTK_MUL_ROWS(extern, true, LM)
+#define X(LM) NTTK_MUL_ROWS(extern, true, LM, false) NTTK_MUL_ROWS(extern, true, LM, true)
 NTTK_ROW_CASES(X)
 #undef X
 template hipError_t mul_rows<true>(const PassArgs&, const PassArgs&, int, hipStream_t);

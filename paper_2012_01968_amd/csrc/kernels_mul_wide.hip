@@ -3,7 +3,7 @@
 
 namespace nttk {
 // row passes: instantiated in kernels_rows.hip
-#define X(LM) NTTK_MUL_ROWS(extern, false, LM)
+#define X(LM) NTTK_MUL_ROWS(extern, false, LM, false) NTTK_MUL_ROWS(extern, false, LM, true)
 NTTK_ROW_CASES(X)
 #undef X
 template hipError_t mul_rows<false>(const PassArgs&, const PassArgs&, int, hipStream_t);

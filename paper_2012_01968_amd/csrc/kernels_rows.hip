@@ -1,5 +1,5 @@
 // Row-pass instances (see NTTK_FWD_ROWS in kernels_impl.hpp): compiled once per direction
-// (NTTK_ROWS_DIR: 0 forward, 1 inverse, 2 key product), arithmetic policy (NTTK_ROWS_FAST)
+// (NTTK_ROWS_DIR: 0 forward, 1 inverse, 2 key product, 3 two-operand product), arithmetic policy (NTTK_ROWS_FAST)
 // and range of row lengths [NTTK_ROWS_LO, NTTK_ROWS_HI] (log2 of the row length).
 #include "kernels_impl.hpp"
 
@@ -8,7 +8,7 @@
 #elif NTTK_ROWS_DIR == 1
 #define NTTK_INST(LM) NTTK_INV_ROWS(, NTTK_ROWS_FAST, LM)
 #else
-#define NTTK_INST(LM) NTTK_MUL_ROWS(, NTTK_ROWS_FAST, LM)
+#define NTTK_INST(LM) NTTK_MUL_ROWS(, NTTK_ROWS_FAST, LM, (NTTK_ROWS_DIR == 3))
 #endif
 
 namespace nttk {

@@ -48,8 +48,12 @@ struct PassArgs {
   // Dense launches only: the first pass of a forward transform may read its input from
   // `src` (same [n_vec][N] layout) instead of `data` (out of place); null = in place.
   const uint64_t* src;
-  // Key-product launches (mul_row): the key vector of vector v is key + v*N (dense) or the
-  // list's key pointer, multiplied in with Barrett constants mu[l], bits[l].
+  // Dense forward column launches over two operands of P / 2 polynomials each (products): the
+  // second operand's output and input; null = one operand.
+  uint64_t* data2;
+  const uint64_t* src2;
+  // Key-product launches (mul_row): the list's key pointer, or (dense, products) the second
+  // operand's vector v at key + v*N, multiplied in with Barrett constants mu[l], bits[l].
   const uint64_t* key;
   const uint64_t* mu;
   const uint32_t* bits;

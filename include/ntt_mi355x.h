@@ -142,7 +142,8 @@ enum { NTT_PATH_AUTO = 0, NTT_PATH_SPLIT = 1, NTT_PATH_FUSED = 2, NTT_PATH_RADIX
  * REQUIRE: each q = 1 mod 2N).  `primes` is a host array of L distinct primes with
  * 2 < q < 2^62 and q = 1 (mod 2N).  The plan computes psi_l, the twiddle tables
  * Psi[i] = psi^{brv(i)} and Psi_inv[i] = psi^{-brv(i)} with their Shoup companions
- * floor(w * 2^64 / q) (Algorithm 4), N^{-1}, and the OT base tables, and uploads
+ * floor(w * 2^64 / q) (Algorithm 4; when every prime is below 2^60, the Montgomery forms that
+ * the kernels multiply by instead, of the same size), N^{-1}, and the OT base tables, and uploads
  * them to the current HIP device.  On success *out holds the plan; on failure *out
  * is set to NULL.  Errors: NTT_ERR_ARG, NTT_ERR_N, NTT_ERR_PRIME, NTT_ERR_NOMEM,
  * NTT_ERR_HIP. */

@@ -105,6 +105,7 @@ struct ntt_plan_s {
   Tw* d_ot_lo_inv = nullptr;
   Tw* d_ot_hi_inv = nullptr;
   Tw* d_scale = nullptr;
+  Tw* d_scale_mul = nullptr;   // d_scale of products (see ntt_domain_product)
   uint64_t* d_mu = nullptr;
   uint32_t* d_bits = nullptr;
   // 32-bit plans: Tw32 {w, floor(w 2^32 / q)} tables, {1/N, Psi_inv[1]/N}, primes, floor(2^64 / q)
@@ -168,7 +169,7 @@ struct ntt_plan_s {
       (void)hipEventDestroy(fused_ev);
     }
     void* ptrs[] = {d_q, d_mc, d_tw_fwd, d_tw_inv, d_ot_lo_fwd, d_ot_hi_fwd, d_ot_lo_inv, d_ot_hi_inv,
-                    d_scale, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_q32, d_mu64,
+                    d_scale, d_scale_mul, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_q32, d_mu64,
                     crt.dec, crt.dec_off, crt.dec_primes, crt.rec, crt.rec_primes, crt.Q};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
@@ -389,7 +390,7 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
   const bool want_ot = b < p->logN;
   const size_t B = want_ot ? (size_t)1 << b : 0, H = want_ot ? NN >> b : 0;
   std::vector<Tw> tw_fwd(L * NN), tw_inv(L * NN), ot_lo_f(L * B), ot_hi_f(L * H), ot_lo_i(L * B), ot_hi_i(L * H),
-      scale(2 * (size_t)L);
+      scale(2 * (size_t)L), scale_mul(2 * (size_t)L);
   std::vector<uint64_t> mu(L), psis(L);
   std::vector<uint32_t> bits(L);
   std::vector<int> bad(L, 0);
@@ -411,39 +412,49 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
       psis[l] = psi;
       const uint64_t psi_inv = nttp::powmod(psi, q - 2, q);
       pw[0] = pwi[0] = 1;
+      const uint64_t psi_b = nttp::shoup_companion(psi, q), psi_inv_b = nttp::shoup_companion(psi_inv, q);
       for (size_t e = 1; e < NN; ++e) {
-        pw[e] = nttp::mulmod(pw[e - 1], psi, q);
-        pwi[e] = nttp::mulmod(pwi[e - 1], psi_inv, q);
+        pw[e] = nttp::mul_shoup(pw[e - 1], psi, psi_b, q);
+        pwi[e] = nttp::mul_shoup(pwi[e - 1], psi_inv, psi_inv_b, q);
       }
+      const nttp::Multiplicand form(q, p->fast);
+      auto entry = [&](uint64_t w) {
+        Tw t;
+        form.put(w, t.w, t.wb);
+        return t;
+      };
       Tw* tf = &tw_fwd[l * NN];
       Tw* ti = &tw_inv[l * NN];
       for (size_t i = 0; i < NN; ++i) {
         const uint32_t e = nttp::bitrev((uint32_t)i, (int)p->logN);
-        tf[i] = Tw{pw[e], nttp::shoup_companion(pw[e], q)};
-        ti[i] = Tw{pwi[e], nttp::shoup_companion(pwi[e], q)};
+        tf[i] = entry(pw[e]);
+        ti[i] = entry(pwi[e]);
+        if (w32) {
+          tw32_f[l * NN + i] = pack32(pw[e], q);
+          tw32_i[l * NN + i] = pack32(pwi[e], q);
+        }
       }
       for (size_t k = 0; k < B; ++k) {
-        ot_lo_f[l * B + k] = Tw{pw[k], nttp::shoup_companion(pw[k], q)};
-        ot_lo_i[l * B + k] = Tw{pwi[k], nttp::shoup_companion(pwi[k], q)};
+        ot_lo_f[l * B + k] = entry(pw[k]);
+        ot_lo_i[l * B + k] = entry(pwi[k]);
       }
       for (size_t h = 0; h < H; ++h) {
-        const uint64_t wf = pw[h << b], wi = pwi[h << b];
-        ot_hi_f[l * H + h] = Tw{wf, nttp::shoup_companion(wf, q)};
-        ot_hi_i[l * H + h] = Tw{wi, nttp::shoup_companion(wi, q)};
+        ot_hi_f[l * H + h] = entry(pw[h << b]);
+        ot_hi_i[l * H + h] = entry(pwi[h << b]);
       }
       const uint64_t n_inv = nttp::powmod(N % q, q - 2, q);
-      const uint64_t w1n = nttp::mulmod(ti[N > 1 ? 1 : 0].w, n_inv, q);
-      scale[2 * l] = Tw{n_inv, nttp::shoup_companion(n_inv, q)};
-      scale[2 * l + 1] = Tw{w1n, nttp::shoup_companion(w1n, q)};
+      const uint64_t w1n = nttp::mulmod(pwi[nttp::bitrev(1u, (int)p->logN)], n_inv, q);
+      scale[2 * l] = entry(n_inv);
+      scale[2 * l + 1] = entry(w1n);
+      // products of fast plans leave a factor 2^-62 (ntt_domain_product), which their scale takes back
+      const uint64_t c62 = p->fast ? ((uint64_t)1 << 62) % q : 1;
+      scale_mul[2 * l] = entry(nttp::mulmod(n_inv, c62, q));
+      scale_mul[2 * l + 1] = entry(nttp::mulmod(w1n, c62, q));
       uint32_t s = 0;
       while (s < 64 && (q >> s)) ++s;
       bits[l] = s;
       mu[l] = (uint64_t)(((nttp::u128)1 << (2 * s)) / q);
       if (w32) {
-        for (size_t i = 0; i < NN; ++i) {
-          tw32_f[l * NN + i] = pack32(tf[i].w, q);
-          tw32_i[l * NN + i] = pack32(ti[i].w, q);
-        }
         scale32[2 * l] = pack32(n_inv, q);
         scale32[2 * l + 1] = pack32(w1n, q);
         q32[l] = (uint32_t)q;
@@ -470,16 +481,21 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
     uint64_t* c = &mod_consts[8 * (size_t)l];
     c[0] = q;
     c[1] = q << 1;
-    c[2] = q << 2;
-    c[3] = 0 - q;
-    c[4] = 0 - (q << 1);
-    c[5] = 0 - (q << 2);
-    c[6] = 0 - (q << 3);
-    c[7] = nttk::quot_estimate_consts(q);
+    if (!p->fast) continue;
+    const int64_t neg = -(int64_t)q;
+    const int32_t nl = (int32_t)(uint32_t)(uint64_t)neg;
+    uint32_t inv = 1;   // q^-1 mod 2^32 by Newton's iteration
+    for (int k = 0; k < 5; ++k) inv *= 2 - (uint32_t)q * inv;
+    int s = 0;
+    while (q >> s) ++s;
+    c[2] = nttp::digits31((int64_t)q);
+    c[3] = (uint32_t)nl | (uint64_t)(uint32_t)(int32_t)((neg - nl) >> 32) << 32;
+    c[4] = (uint32_t)(0u - inv) << 1;
+    c[5] = (uint64_t)(((nttp::u128)1 << (s + 6)) / q) | (uint64_t)(s - 3) << 32;
   }
 
   if (w32) {   // a 32-bit plan keeps only its 32-bit tables on the device
-    for (auto* v : {&tw_fwd, &tw_inv, &ot_lo_f, &ot_hi_f, &ot_lo_i, &ot_hi_i, &scale}) std::vector<Tw>().swap(*v);
+    for (auto* v : {&tw_fwd, &tw_inv, &ot_lo_f, &ot_hi_f, &ot_lo_i, &ot_hi_i, &scale, &scale_mul}) std::vector<Tw>().swap(*v);
   }
   if (hipGetDevice(&p->device) != hipSuccess) return fail(NTT_ERR_HIP, "hipGetDevice failed");
   hipError_t e;
@@ -498,7 +514,7 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
       (e = upload(&p->d_tw_fwd, tw_fwd)) != hipSuccess ||
       (e = upload(&p->d_tw_inv, tw_inv)) != hipSuccess || (e = upload(&p->d_ot_lo_fwd, ot_lo_f)) != hipSuccess ||
       (e = upload(&p->d_ot_hi_fwd, ot_hi_f)) != hipSuccess || (e = upload(&p->d_ot_lo_inv, ot_lo_i)) != hipSuccess ||
-      (e = upload(&p->d_ot_hi_inv, ot_hi_i)) != hipSuccess || (e = upload(&p->d_scale, scale)) != hipSuccess ||
+      (e = upload(&p->d_ot_hi_inv, ot_hi_i)) != hipSuccess || (e = upload(&p->d_scale, scale)) != hipSuccess || (e = upload(&p->d_scale_mul, scale_mul)) != hipSuccess ||
       (e = upload(&p->d_mu, mu)) != hipSuccess || (e = upload(&p->d_bits, bits)) != hipSuccess) {
     if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of plan tables failed");
     return hip_fail(e, "uploading plan tables");
@@ -622,7 +638,8 @@ static hipError_t polymul_enqueue(ntt_plan_t plan, const uint64_t* d_a, const ui
   const int ot = plan->active_ot();
   if (plan->kernel_path == NTT_PATH_SPLIT) {
     PassArgs rows = plan->args(d_c, n_polys, false);
-    const PassArgs inv = plan->args(d_c, n_polys, true);
+    PassArgs inv = plan->args(d_c, n_polys, true);
+    inv.scale = plan->d_scale_mul;
     if (plan->logN1) {
       PassArgs cols = rows;
       cols.src = d_a;
@@ -728,6 +745,12 @@ struct ntt_batch_s {
     return a;
   }
 
+  PassArgs full_inverse_args(const Group& g) const {
+    PassArgs a = list_args(g, g.off_full, g.n_full, true);
+    a.scale = g.plan->d_scale_mul;
+    return a;
+  }
+
   // Enqueue the grouped work in three phases over all plans: forward transforms, then key
   // products, then inverse transforms.  Vectors of jobs that do all three ("full") take the
   // forward column pass in phase 0, the row passes with the key product (one launch) in
@@ -753,8 +776,8 @@ struct ntt_batch_s {
                                            g.plan->d_bits, st)) != hipSuccess)
         return e;
       if (g.n_full &&
-          (e = nttk::launch_mul_rows(list_args(g, g.off_full, g.n_full, false),
-                                     list_args(g, g.off_full, g.n_full, true), ot, st)) != hipSuccess)
+          (e = nttk::launch_mul_rows(list_args(g, g.off_full, g.n_full, false), full_inverse_args(g), ot, st)) !=
+              hipSuccess)
         return e;
       return hipSuccess;
     }
@@ -768,7 +791,7 @@ struct ntt_batch_s {
       if (nat && !inv && (e = nttk::launch_brv_permute(a, st)) != hipSuccess) return e;
     }
     if (g.n_full && split) {
-      const PassArgs a = list_args(g, g.off_full, g.n_full, inv);
+      const PassArgs a = inv ? full_inverse_args(g) : list_args(g, g.off_full, g.n_full, false);
       if ((e = inv ? nttk::launch_inverse_pass(a, ot, 1, st) : nttk::launch_forward_pass(a, ot, 0, st)) !=
           hipSuccess)
         return e;

@@ -95,7 +95,7 @@ __device__ __forceinline__ void fwd_col_tile(const PassArgs& a, uint32_t v, uint
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = lds[S::template idx<k>(t, u) * F::C + c];
     }
-    ct_step<FAST, LOGM1, kFusedLR, k, 0>(x, t, 1u, tabfn, ot, md);
+    ct_step<FAST, LOGM1, kFusedLR, k, 0, kCtCanon>(x, t, 1u, tabfn, ot, md);
   });
 #pragma unroll
   for (int u = 0; u < S::R; ++u) colp[(size_t)S::template idx<S::K - 1>(t, u) << LOGM2] = x[u];
@@ -135,7 +135,7 @@ __device__ __forceinline__ void fwd_row_tile(const PassArgs& a, uint32_t v, uint
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = l[RC::at(S::template idx<k>(t, u))];
     }
-    ct_step<FAST, LOGM2, kFusedLR, k, OTS>(x, t, base, tabfn, ot, md);
+    ct_step<FAST, LOGM2, kFusedLR, k, OTS, kCtLazy>(x, t, base, tabfn, ot, md);
   });
 #pragma unroll
   for (int u = 0; u < S::R; ++u) x[u] = A::fwd_final(x[u], md);
@@ -193,7 +193,7 @@ __device__ __forceinline__ void inv_row_tile(const PassArgs& a, uint32_t v, uint
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = l[RC::at(S::template idx<k>(t, u))];
     }
-    gs_step<FAST, LOGM2, kFusedLR, k, OTS, false>(x, t, base, tabfn, ot, md, sc, sc);
+    gs_step<FAST, LOGM2, kFusedLR, k, OTS, false, kGsLazy>(x, t, base, tabfn, ot, md, sc, sc);
   });
 #pragma unroll
   for (int u = 0; u < S::R; ++u) rowp[S::template idx<0>(t, u)] = x[u];
@@ -226,7 +226,7 @@ __device__ __forceinline__ void inv_col_tile(const PassArgs& a, uint32_t v, uint
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = lds[S::template idx<k>(t, u) * F::C + c];
     }
-    gs_step<FAST, LOGM1, kFusedLR, k, 0, true>(x, t, 1u, tabfn, ot, md, sc0, sc1);
+    gs_step<FAST, LOGM1, kFusedLR, k, 0, true, kGsLazy>(x, t, 1u, tabfn, ot, md, sc0, sc1);
   });
 #pragma unroll
   for (int u = 0; u < S::R; ++u) colp[(size_t)S::template idx<0>(t, u) << LOGM2] = A::inv_final(x[u], md);

@@ -129,13 +129,14 @@ struct RowRef {
 // Row v of this workgroup's tile.  When V divides N1 (every split launch with at least V
 // rows per vector) the tile's rows are consecutive rows of one vector, so the vector is
 // looked up once per workgroup; otherwise each row finds its own vector.
-template <typename C>
+// ONEP: single-pass launches (N1 = 1); the others have N1 >= 16.
+template <typename C, bool ONEP>
 __device__ __forceinline__ RowRef row_ref(const PassArgs& a, uint32_t v) {
   const uint64_t rows = a.n_vec << a.logN1;
   const uint32_t n_tiles = (uint32_t)((rows + C::V - 1) / C::V);
   const uint32_t tile = __builtin_amdgcn_readfirstlane(xcd_tile(n_tiles, a.debug));
   const uint32_t N1 = 1u << a.logN1;
-  if ((uint32_t)C::V <= N1) {
+  if ((!ONEP && C::V <= 16) || (uint32_t)C::V <= N1) {
     const bool valid = tile < n_tiles;
     const uint32_t tl = valid ? tile : 0;
     gu64* vb;
@@ -183,7 +184,16 @@ __device__ __forceinline__ RowRef row_ref(const PassArgs& a, uint32_t v) {
   return RowRef{vr.base + off, sb + off, kb ? kb + off : nullptr, vr.limb, N1 + r, valid};
 }
 
-template <bool FAST, int LOGM, int OTS, int NTH, int LRR>
+// The row's prime, as a scalar where the rows of a wave share it (one row per wave, or the rows of
+// one vector), so that its constants load into SGPRs: 16 VGPRs fewer.
+template <typename C, bool ONEP>
+__device__ __forceinline__ uint32_t wave_limb(const RowRef& rr) {
+  if constexpr (C::T >= 64 || (!ONEP && C::V <= 16)) return __builtin_amdgcn_readfirstlane(rr.limb);
+  else return rr.limb;
+}
+
+// ONEP: single-pass transform (N1 = 1), which reads the caller's canonical input.
+template <bool FAST, int LOGM, int OTS, bool ONEP, int NTH, int LRR>
 __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void fwd_row_kernel(PassArgs a) {
   using A = Arith<FAST>;
   using C = RowCfg<LOGM, NTH, LRR>;
@@ -191,9 +201,9 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void fwd_row_kernel(P
   __shared__ uint64_t lds[C::V * C::PITCH];
   const uint32_t tid = threadIdx.x, v = tid / C::T, t = tid % C::T;
   poison_lds<C::V * C::PITCH>(lds, a.debug, tid, C::NT);
-  const RowRef rr = row_ref<C>(a, v);
+  const RowRef rr = row_ref<C, ONEP>(a, v);
   const bool valid = rr.valid;
-  const uint32_t limb = rr.limb;
+  const uint32_t limb = wave_limb<C, ONEP>(rr);
   const Mod md = Mod::load((cu64*)a.mc + 8 * (size_t)limb);
   const uint32_t base = rr.base;
   const Tw* tab = a.tw + ((size_t)limb << a.logN);
@@ -243,8 +253,9 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void fwd_row_kernel(P
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = l[C::at(S::template idx<k>(t, u))];
     }
-    if constexpr (kRowPreload) ct_step<FAST, LOGM, C::LR, k, OTS>(x, t, base, tabfn, ot, md, pre);
-    else ct_step<FAST, LOGM, C::LR, k, OTS>(x, t, base, tabfn, ot, md);
+    constexpr int IN = ONEP ? kCtCanon : kCtLazy;
+    if constexpr (kRowPreload) ct_step<FAST, LOGM, C::LR, k, OTS, IN>(x, t, base, tabfn, ot, md, pre);
+    else ct_step<FAST, LOGM, C::LR, k, OTS, IN>(x, t, base, tabfn, ot, md);
   });
 
 #pragma unroll
@@ -289,9 +300,9 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void inv_row_kernel(P
   __shared__ uint64_t lds[C::V * C::PITCH];
   const uint32_t tid = threadIdx.x, v = tid / C::T, t = tid % C::T;
   poison_lds<C::V * C::PITCH>(lds, a.debug, tid, C::NT);
-  const RowRef rr = row_ref<C>(a, v);
+  const RowRef rr = row_ref<C, SCALE0>(a, v);
   const bool valid = rr.valid;
-  const uint32_t limb = rr.limb;
+  const uint32_t limb = wave_limb<C, SCALE0>(rr);
   const Mod md = Mod::load((cu64*)a.mc + 8 * (size_t)limb);
   const uint32_t base = rr.base;
   const Tw* tab = a.tw + ((size_t)limb << a.logN);
@@ -350,9 +361,9 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void inv_row_kernel(P
       for (int u = 0; u < S::R; ++u) x[u] = l[C::at(S::template idx<k>(t, u))];
     }
     // the first register step sees the caller's canonical input
-    constexpr int IN_B = k == S::K - 1 ? 1 : 8;
-    if constexpr (kRowPreload) gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, IN_B>(x, t, base, tabfn, ot, md, sc0, sc1, pre);
-    else gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, IN_B>(x, t, base, tabfn, ot, md, sc0, sc1);
+    constexpr int IN = k == S::K - 1 ? kGsCanon : kGsLazy;
+    if constexpr (kRowPreload) gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, IN>(x, t, base, tabfn, ot, md, sc0, sc1, pre);
+    else gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, IN>(x, t, base, tabfn, ot, md, sc0, sc1);
   });
 
   if constexpr (SCALE0) {
@@ -394,9 +405,9 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
   __shared__ uint64_t lds[BUFS * C::V * C::PITCH];
   const uint32_t tid = threadIdx.x, v = tid / C::T, t = tid % C::T;
   poison_lds<BUFS * C::V * C::PITCH>(lds, af.debug, tid, C::NT);
-  const RowRef rr = row_ref<C>(af, v);
+  const RowRef rr = row_ref<C, SCALE0>(af, v);
   const bool valid = rr.valid;
-  const uint32_t limb = rr.limb;
+  const uint32_t limb = wave_limb<C, SCALE0>(rr);
   const Mod md = Mod::load((cu64*)af.mc + 8 * (size_t)limb);
   const uint32_t base = rr.base;
   const Tw* tabf = af.tw + ((size_t)limb << af.logN);
@@ -474,19 +485,24 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
         for (int u = 0; u < S::R; ++u) y[u] = l2[C::at(S::template idx<k>(t, u))];
       }
     }
-    ct_step<FAST, LOGM, C::LR, k, OTS>(x, t, base, tabfnf, otf, md, pre);
-    if constexpr (PAIR) ct_step<FAST, LOGM, C::LR, k, OTS>(y, t, base, tabfnf, otf, md, pre);
+    constexpr int IN = SCALE0 ? kCtCanon : kCtLazy;
+    ct_step<FAST, LOGM, C::LR, k, OTS, IN>(x, t, base, tabfnf, otf, md, pre);
+    if constexpr (PAIR) ct_step<FAST, LOGM, C::LR, k, OTS, IN>(y, t, base, tabfnf, otf, md, pre);
   });
-  // canonical NTT-domain values times the second factor at the same positions
+  // times the second factor at the same positions
   if (valid) {
-    const uint64_t mu = ((cu64*)af.mu)[limb];
-    const uint32_t bits = ((const __attribute__((address_space(4))) uint32_t*)af.bits)[limb];
+    uint64_t mu = 0;
+    uint32_t bits = 0;
+    if constexpr (!FAST) {
+      mu = ((cu64*)af.mu)[limb];
+      bits = ((const __attribute__((address_space(4))) uint32_t*)af.bits)[limb];
+    }
 #pragma unroll
     for (int u = 0; u < S::R; ++u) {
       uint64_t f;
-      if constexpr (PAIR) f = A::fwd_final(y[u], md);
+      if constexpr (PAIR) f = y[u];
       else f = rr.keyp[S::template idx<S::K - 1>(t, u)];
-      x[u] = mulmod_barrett(A::fwd_final(x[u], md), f, md.q, mu, bits);
+      x[u] = ntt_domain_product<FAST, PAIR>(x[u], f, md, mu, bits);
     }
   }
   static_for_down<S::K, 0>([&](auto kc) {
@@ -505,8 +521,8 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = l[C::at(S::template idx<k>(t, u))];
     }
-    // the product leaves canonical values (padding rows skip it, but are never stored)
-    gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, k == S::K - 1 ? 1 : 8>(x, t, base, tabfni, oti, md, sc0, sc1, pre);
+    // the product leaves values within q of 0 (padding rows skip it, but are never stored)
+    gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, k == S::K - 1 ? kGsCanon : kGsLazy>(x, t, base, tabfni, oti, md, sc0, sc1, pre);
   });
   if constexpr (SCALE0) {
 #pragma unroll
@@ -557,7 +573,7 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void fwd_col_kernel(PassA
   }
   const uint32_t cg = tile % groups;
   const VecRef vr = vec_ref(a, vec);
-  const uint32_t limb = vr.limb;
+  const uint32_t limb = __builtin_amdgcn_readfirstlane(vr.limb);   // one vector per workgroup
   const Mod md = Mod::load((cu64*)a.mc + 8 * (size_t)limb);
   const Tw* tab = a.tw + ((size_t)limb << a.logN);
   gu64* colp = vr.base + cg * C::W + c;
@@ -581,7 +597,7 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void fwd_col_kernel(PassA
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = lds[C::at(S::template idx<k>(t, u)) + c];
     }
-    ct_step<FAST, LOGM, kLR, k, 0>(x, t, 1u, tabfn, ot, md);
+    ct_step<FAST, LOGM, kLR, k, 0, kCtCanon>(x, t, 1u, tabfn, ot, md);
   });
 
 #pragma unroll
@@ -605,7 +621,7 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void inv_col_kernel(PassA
   const uint64_t vec = a.vecs ? tile / groups : limb_major_vec(tile / groups, a.L, a.P);
   const uint32_t cg = tile % groups;
   const VecRef vr = vec_ref(a, vec);
-  const uint32_t limb = vr.limb;
+  const uint32_t limb = __builtin_amdgcn_readfirstlane(vr.limb);   // one vector per workgroup
   const Mod md = Mod::load((cu64*)a.mc + 8 * (size_t)limb);
   const Tw* tab = a.tw + ((size_t)limb << a.logN);
   const Tw sc0 = a.scale[2 * limb], sc1 = a.scale[2 * limb + 1];
@@ -628,7 +644,7 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void inv_col_kernel(PassA
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = lds[C::at(S::template idx<k>(t, u)) + c];
     }
-    gs_step<FAST, LOGM, kLR, k, 0, true>(x, t, 1u, tabfn, ot, md, sc0, sc1);
+    gs_step<FAST, LOGM, kLR, k, 0, true, kGsLazy>(x, t, 1u, tabfn, ot, md, sc0, sc1);
   });
 
 #pragma unroll
@@ -657,12 +673,12 @@ __host__ hipError_t with_row_shape(const PassArgs& a, F&& f) {
   return hipErrorInvalidValue;
 }
 
-template <bool FAST, int LOGM, int OTS, int NTH, int LRR>
+template <bool FAST, int LOGM, int OTS, bool ONEP, int NTH, int LRR>
 hipError_t go_fwd_row(const PassArgs& a, hipStream_t st) {
   using C = RowCfg<LOGM, NTH, LRR>;
   const uint64_t rows = a.n_vec << a.logN1;
   const uint64_t blocks = ((rows + C::V - 1) / C::V + 7) / 8 * 8;
-  hipLaunchKernelGGL((fwd_row_kernel<FAST, LOGM, OTS, NTH, LRR>), dim3((uint32_t)blocks), dim3(C::NT), 0, st, a);
+  hipLaunchKernelGGL((fwd_row_kernel<FAST, LOGM, OTS, ONEP, NTH, LRR>), dim3((uint32_t)blocks), dim3(C::NT), 0, st, a);
   return hipGetLastError();
 }
 
@@ -735,9 +751,15 @@ template <bool FAST, int LM>
 hipError_t fwd_row_lm(const PassArgs& a, int ots, hipStream_t st) {
   return with_row_shape<LM>(a, [&](auto nth, auto lr) {
     constexpr int NTH = decltype(nth)::value, LRR = decltype(lr)::value;
-    if (ots == 0) return go_fwd_row<FAST, LM, 0, NTH, LRR>(a, st);
-    if (ots == 1) return go_fwd_row<FAST, LM, 1, NTH, LRR>(a, st);
-    if (ots == 2) return go_fwd_row<FAST, LM, 2, NTH, LRR>(a, st);
+    if (a.logN1 == 0) {
+      if (ots == 0) return go_fwd_row<FAST, LM, 0, true, NTH, LRR>(a, st);
+      if constexpr (LM >= 2) if (ots == 1) return go_fwd_row<FAST, LM, 1, true, NTH, LRR>(a, st);
+      if constexpr (LM >= 3) if (ots == 2) return go_fwd_row<FAST, LM, 2, true, NTH, LRR>(a, st);
+    } else if constexpr (LM >= 4) {   // a split has rows of at least 16 points
+      if (ots == 0) return go_fwd_row<FAST, LM, 0, false, NTH, LRR>(a, st);
+      if (ots == 1) return go_fwd_row<FAST, LM, 1, false, NTH, LRR>(a, st);
+      if (ots == 2) return go_fwd_row<FAST, LM, 2, false, NTH, LRR>(a, st);
+    }
     return hipErrorInvalidValue;
   });
 }
@@ -762,7 +784,7 @@ hipError_t inv_row_lm(const PassArgs& a, int ots, bool scale0, hipStream_t st) {
       if (ots == 0) return go_inv_row<FAST, LM, 0, true, NTH, LRR>(a, st);
       if constexpr (LM >= 2) if (ots == 1) return go_inv_row<FAST, LM, 1, true, NTH, LRR>(a, st);
       if constexpr (LM >= 3) if (ots == 2) return go_inv_row<FAST, LM, 2, true, NTH, LRR>(a, st);
-    } else {
+    } else if constexpr (LM >= 4) {
       if (ots == 0) return go_inv_row<FAST, LM, 0, false, NTH, LRR>(a, st);
       if (ots == 1) return go_inv_row<FAST, LM, 1, false, NTH, LRR>(a, st);
       if (ots == 2) return go_inv_row<FAST, LM, 2, false, NTH, LRR>(a, st);
@@ -825,7 +847,7 @@ hipError_t mul_rows_lm(const PassArgs& af, const PassArgs& ai, int ots, bool sca
       if (ots == 0) return go_mul_row<FAST, LM, 0, true, NTH, LRR, PAIR>(af, ai, st);
       if constexpr (LM >= 2) if (ots == 1) return go_mul_row<FAST, LM, 1, true, NTH, LRR, PAIR>(af, ai, st);
       if constexpr (LM >= 3) if (ots == 2) return go_mul_row<FAST, LM, 2, true, NTH, LRR, PAIR>(af, ai, st);
-    } else {
+    } else if constexpr (LM >= 4) {
       if (ots == 0) return go_mul_row<FAST, LM, 0, false, NTH, LRR, PAIR>(af, ai, st);
       if (ots == 1) return go_mul_row<FAST, LM, 1, false, NTH, LRR, PAIR>(af, ai, st);
       if (ots == 2) return go_mul_row<FAST, LM, 2, false, NTH, LRR, PAIR>(af, ai, st);

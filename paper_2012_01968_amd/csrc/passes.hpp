@@ -37,7 +37,8 @@ struct PassArgs {
   const Tw* ot_lo;       // [L][B]     psi^{+-k},     k < B       (OT only)
   const Tw* ot_hi;       // [L][N/B]   psi^{+-B*h},   h < N/B     (OT only)
   const uint64_t* q;     // [L]
-  const Tw* scale;       // [L][2]: {1/N}, {Psi_inv[1]/N}        (inverse only)
+  const Tw* scale;       // [L][2]: {1/N}, {Psi_inv[1]/N}        (inverse only; products: times the
+                         // factor that ntt_domain_product leaves)
   uint64_t n_vec;        // vectors in the batch (n_polys * L)
   uint32_t P;            // polynomials in the batch
   uint32_t L;
@@ -57,11 +58,7 @@ struct PassArgs {
   const uint64_t* key;
   const uint64_t* mu;
   const uint32_t* bits;
-  // [L][8] per-prime constants {q, 2q, 4q, -q, -2q, -4q, -8q, quotient-estimate constants}
-  // (Mod::load).
-  // Loaded rather than derived from q in the kernel, so that the compiler adds them as
-  // 64-bit operands instead of re-deriving them from q's halves.
-  const uint64_t* mc;
+  const uint64_t* mc;    // [L][8] per-prime constants (Mod::load)
   // Tile shape of the split passes (0 = the built-in default): row pass values per lane as
   // log2 (2 or 3) and workgroup lanes (64, 128 or 256); column pass width in adjacent
   // columns (16, 32, 64, 128 or 256).
@@ -181,8 +178,9 @@ __device__ __forceinline__ void load_step_twiddles(Tw (&w)[NR], Tw (&w2)[NR], ui
 // Forward (Cooley-Tukey) register step K_STEP on the R values of one lane.
 // TabFn(ix) returns the table twiddle Psi[ix]; the last OTS stages of this
 // sub-transform take their twiddles from `ot` instead.
+// IN: bound of the sub-transform's inputs (CtRange; fast policy only).
 // Pre: NoTw, or a struct with arrays w[R], w2[R] filled by load_step_twiddles.
-template <bool FAST, int LOGM, int LR, int K_STEP, int OTS, int NR, typename TabFn, typename Pre = NoTw>
+template <bool FAST, int LOGM, int LR, int K_STEP, int OTS, int IN, int NR, typename TabFn, typename Pre = NoTw>
 __device__ __forceinline__ void ct_step(uint64_t (&x)[NR], uint32_t t, uint32_t base,
                                         TabFn&& tab, const OtTables& ot, const Mod& md, const Pre& pre = Pre{}) {
   constexpr bool PRE = !std::is_same<Pre, NoTw>::value;
@@ -215,12 +213,11 @@ __device__ __forceinline__ void ct_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
         }
         ys[k] = x[u | (1 << i)];
       }
-      // X is reduced by 8q in even stages only: values stay below 16q (see modarith.hpp)
-      constexpr bool reduce = (s % 2) == 0;
+      constexpr bool reduce = CtRange<IN>::reduce(s);
 #pragma unroll
       for (int k = 0; k < H; ++k) {
         const int u = ((k >> i) << (i + 1)) | (k & ((1 << i) - 1));
-        xs[k] = reduce ? csub_sign(x[u], md.nq8) : x[u];
+        xs[k] = reduce ? A::reduce(x[u], md) : x[u];
       }
       A::template mul_n<H>(v, ys, w, md);
       if constexpr (OTS > 0 && s >= LOGM - OTS) A::template mul_n<H>(v, v, w2, md);
@@ -228,7 +225,7 @@ __device__ __forceinline__ void ct_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
       for (int k = 0; k < H; ++k) {
         const int u = ((k >> i) << (i + 1)) | (k & ((1 << i) - 1));
         x[u] = xs[k] + v[k];
-        x[u | (1 << i)] = xs[k] + md.q4 - v[k];
+        x[u | (1 << i)] = xs[k] - v[k];
       }
     } else {
 #pragma unroll
@@ -257,28 +254,10 @@ __device__ __forceinline__ void ct_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
 }
 
 // Inverse (Gentleman-Sande) register step K_STEP: stages from the low bit up.
-// Value bounds of the fast Gentleman-Sande stages, in multiples of q.  The register step's
-// inputs lie below IN_B q (IN_B <= 8).  In the local stage i of a step, register u (bit i
-// clear) pairs with u | 2^i; both played the same part in the stage before (bit i-1 of u),
-// so they share a bound.  A product is below 4q whatever it multiplied; a sum doubles the
-// bound and is reduced by 8q only when that would pass 8q.  So a sum of two products needs
-// no reduction, and everything stays below 8q.
-template <int IN_B>
-struct GsRange {
-  static_assert(IN_B >= 1 && IN_B <= 8, "Gentleman-Sande inputs must lie below 8q");
-  // bound of register u before local stage i
-  static constexpr int before(int i, int u) {
-    int b = IN_B;
-    for (int j = 0; j < i; ++j) b = (u >> j) & 1 ? 4 : (2 * b > 8 ? 8 : 2 * b);
-    return b;
-  }
-  static constexpr bool reduce(int i, int u) { return 2 * before(i, u) > 8; }
-};
-
 // SCALE0: this sub-transform holds stage 0 of the whole transform, whose butterfly
 // also applies the 1/N scale (sc0 = 1/N, sc1 = Psi_inv[1]/N).
-// IN_B: the step's inputs lie below IN_B q (fast policy; 1 for canonical inputs).
-template <bool FAST, int LOGM, int LR, int K_STEP, int OTS, bool SCALE0, int IN_B = 8, int NR, typename TabFn,
+// IN: bound of the step's inputs (GsRange; fast policy only).
+template <bool FAST, int LOGM, int LR, int K_STEP, int OTS, bool SCALE0, int IN, int NR, typename TabFn,
           typename Pre = NoTw>
 __device__ __forceinline__ void gs_step(uint64_t (&x)[NR], uint32_t t, uint32_t base,
                                         TabFn&& tab, const OtTables& ot, const Mod& md,
@@ -293,7 +272,12 @@ __device__ __forceinline__ void gs_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
     constexpr int bit = decltype(bit_c)::value;
     constexpr int s = LOGM - 1 - bit;
     constexpr int i = bit - lo;
-    if constexpr (FAST && !(SCALE0 && s == 0)) {
+    if constexpr (FAST) {
+     if constexpr (SCALE0 && s == 0) {
+#pragma unroll
+      for (int u = 0; u < S::R; ++u)
+        if (!(u & (1 << i))) A::gs_scaled(x[u], x[u | (1 << i)], sc1, sc0, md);
+     } else {
       constexpr int H = S::R / 2;
       Tw w[H], w2[H];
       uint64_t ds[H], v[H];
@@ -315,9 +299,8 @@ __device__ __forceinline__ void gs_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
       for (int k = 0; k < H; ++k) {
         const int u = ((k >> i) << (i + 1)) | (k & ((1 << i) - 1));
         const uint64_t X = x[u], Y = x[u | (1 << i)];
-        const int b = GsRange<IN_B>::before(i, u);   // folded: i and (after unrolling) u are constants
-        ds[k] = X + (b == 1 ? md.q : b == 2 ? md.q2 : b == 4 ? md.q4 : md.q8) - Y;
-        x[u] = GsRange<IN_B>::reduce(i, u) ? csub_sign(X + Y, md.nq8) : X + Y;
+        ds[k] = X - Y;
+        x[u] = GsRange<IN>::reduce(i, u) ? A::reduce(X + Y, md) : X + Y;   // folded: i, u are constants
       }
       A::template mul_n<H>(v, ds, w, md);
       if constexpr (OTS > 0 && s >= LOGM - OTS) A::template mul_n<H>(v, v, w2, md);
@@ -326,6 +309,7 @@ __device__ __forceinline__ void gs_step(uint64_t (&x)[NR], uint32_t t, uint32_t 
         const int u = ((k >> i) << (i + 1)) | (k & ((1 << i) - 1));
         x[u | (1 << i)] = v[k];
       }
+     }
     } else {
 #pragma unroll
     for (int u = 0; u < S::R; ++u) {

@@ -53,6 +53,42 @@ inline bool is_prime(uint64_t n) {
 // Shoup companion floor(w * 2^64 / q) of a fixed multiplicand w < q (Algorithm 4).
 inline uint64_t shoup_companion(uint64_t w, uint64_t q) { return (uint64_t)(((u128)w << 64) / q); }
 
+// a * w mod q with the companion wb of w, any a < 2^64.
+inline uint64_t mul_shoup(uint64_t a, uint64_t w, uint64_t wb, uint64_t q) {
+  const uint64_t r = a * w - (uint64_t)(((u128)a * wb) >> 64) * q;
+  return r >= q ? r - q : r;
+}
+
+// Signed digits of v, low one in [-2^30, 2^30): d0 | d1 << 32 with v = d1 2^31 + d0.
+inline uint64_t digits31(int64_t v) {
+  const int32_t d0 = (int32_t)((uint32_t)v << 1) >> 1;
+  return (uint32_t)d0 | (uint64_t)(uint32_t)(int32_t)((v - d0) >> 31) << 32;
+}
+
+// What the kernels keep of one fixed multiplicand w < q (nttk::Tw): w and its Shoup companion, or,
+// for primes below 2^60, the digits of w 2^31 and w 2^63 mod q, centred (signed_mont.hpp).
+struct Multiplicand {
+  uint64_t q;
+  bool mont;
+  uint64_t c31, c31b, c63, c63b;
+  Multiplicand(uint64_t q_, bool mont_) : q(q_), mont(mont_) {
+    c31 = ((uint64_t)1 << 31) % q;
+    c63 = ((uint64_t)1 << 63) % q;
+    c31b = shoup_companion(c31, q);
+    c63b = shoup_companion(c63, q);
+  }
+  uint64_t centred(uint64_t v) const { return digits31(v > q / 2 ? (int64_t)v - (int64_t)q : (int64_t)v); }
+  void put(uint64_t w, uint64_t& a, uint64_t& b) const {
+    if (mont) {
+      a = centred(mul_shoup(w, c31, c31b, q));
+      b = centred(mul_shoup(w, c63, c63b, q));
+    } else {
+      a = w;
+      b = shoup_companion(w, q);
+    }
+  }
+};
+
 inline uint32_t bitrev(uint32_t x, int bits) {
   uint32_t r = 0;
   for (int i = 0; i < bits; ++i) {
@@ -77,10 +113,10 @@ inline uint64_t smallest_primitive_root(uint64_t q, uint64_t N) {
     }
   }
   if (!r0) return 0;
-  const uint64_t r2 = mulmod(r0, r0, q);
+  const uint64_t r2 = mulmod(r0, r0, q), r2b = shoup_companion(r2, q);
   uint64_t best = r0, cur = r0;
   for (uint64_t k = 1; k < N; ++k) {
-    cur = mulmod(cur, r2, q);
+    cur = mul_shoup(cur, r2, r2b, q);
     if (cur < best) best = cur;
   }
   return best;

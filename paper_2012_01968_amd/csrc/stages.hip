@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kStageThreads) void stage_group_kernel(PassArgs a, 
 #pragma unroll
   for (int u = 0; u < R; ++u) x[u] = p[(size_t)u << lo];
   if constexpr (!INV) {
-    ct_step<FAST, K, K, 0, 0>(x, 0u, base, tabfn, ot, md);
+    ct_step<FAST, K, K, 0, 0, kCtLazy>(x, 0u, base, tabfn, ot, md);
     if constexpr (FINAL) {
 #pragma unroll
       for (int u = 0; u < R; ++u) x[u] = A::fwd_final(x[u], md);
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kStageThreads) void stage_group_kernel(PassArgs a, 
       sc0 = a.scale[2 * vr.limb];
       sc1 = a.scale[2 * vr.limb + 1];
     }
-    gs_step<FAST, K, K, 0, 0, SCALE0, CANON_IN ? 1 : 8>(x, 0u, base, tabfn, ot, md, sc0, sc1);
+    gs_step<FAST, K, K, 0, 0, SCALE0, CANON_IN ? kGsCanon : kGsLazy>(x, 0u, base, tabfn, ot, md, sc0, sc1);
     if constexpr (SCALE0) {
 #pragma unroll
       for (int u = 0; u < R; ++u) x[u] = A::inv_final(x[u], md);

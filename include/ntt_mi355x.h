@@ -311,8 +311,7 @@ ntt_status ntt_batch_destroy(ntt_batch_t batch);
  *
  * The word-size choice of Section IV taken the other way: a plan created with word_bits = 32
  * holds residues in uint32_t words, for primes below 2^30 (four times a prime fits a word,
- * so the lazy butterfly ranges hold), and Shoup products of one high and two low 32x32
- * multiplies.  The same modulus budget takes twice the limbs of 64-bit words.  Such a plan
+ * so the lazy butterfly ranges hold), and Montgomery products by one-word multiplicands.  The same modulus budget takes twice the limbs of 64-bit words.  Such a plan
  * takes table twiddles, the split (or single-pass) kernels and bit-reversed order; other
  * options return NTT_ERR_UNSUPPORTED and primes at or above 2^30 NTT_ERR_PRIME.  Its data
  * goes through the _u32 calls below ([n_polys][L][N] uint32_t, device, 16-byte aligned),

@@ -108,10 +108,13 @@ struct ntt_plan_s {
   Tw* d_scale_mul = nullptr;   // d_scale of products (see ntt_domain_product)
   uint64_t* d_mu = nullptr;
   uint32_t* d_bits = nullptr;
-  // 32-bit plans: Tw32 {w, floor(w 2^32 / q)} tables, {1/N, Psi_inv[1]/N}, primes, floor(2^64 / q)
-  void* d_tw32_fwd = nullptr;
-  void* d_tw32_inv = nullptr;
-  void* d_scale32 = nullptr;
+  // 32-bit plans: tables of w 2^32 mod q (centred), {1/N, Psi_inv[1]/N} and the same of products,
+  // {q, -q^-1 mod 2^32}, primes, floor(2^64 / q)
+  int32_t* d_tw32_fwd = nullptr;
+  int32_t* d_tw32_inv = nullptr;
+  int32_t* d_scale32 = nullptr;
+  int32_t* d_scale32_mul = nullptr;
+  nttk::Prime32* d_primes32 = nullptr;
   uint32_t* d_q32 = nullptr;
   uint64_t* d_mu64 = nullptr;
 
@@ -169,7 +172,8 @@ struct ntt_plan_s {
       (void)hipEventDestroy(fused_ev);
     }
     void* ptrs[] = {d_q, d_mc, d_tw_fwd, d_tw_inv, d_ot_lo_fwd, d_ot_hi_fwd, d_ot_lo_inv, d_ot_hi_inv,
-                    d_scale, d_scale_mul, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_q32, d_mu64,
+                    d_scale, d_scale_mul, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul,
+                    d_primes32, d_q32, d_mu64,
                     crt.dec, crt.dec_off, crt.dec_primes, crt.rec, crt.rec_primes, crt.Q};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
@@ -200,6 +204,9 @@ struct ntt_plan_s {
     a.col_w = col_w;
     a.debug = debug;
     return a;
+  }
+  nttk::Plan32 plan32() const {
+    return nttk::Plan32{d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul, d_primes32, L, logN, logN1};
   }
   int active_ot() const { return twiddle_mode == NTT_TWIDDLE_OT ? ot_stages : 0; }
   // the paths whose data goes back to global memory after every group of stages
@@ -308,7 +315,9 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
     // 32-bit words: table twiddles, one or two passes, Algorithm 1's order
     if (mode == NTT_TWIDDLE_OT || stage_path || o.kernel_path == NTT_PATH_FUSED || o.order != NTT_ORDER_BITREV)
       return fail(NTT_ERR_UNSUPPORTED, "32-bit plans take table twiddles, the split path and bit-reversed order");
-    p->logN1 = o.log2_n1 == 0 ? (p->logN <= 12 ? 0 : p->logN / 2) : (o.log2_n1 < 0 ? 0 : (uint32_t)o.log2_n1);
+    // automatic: rows of 2^7 .. 2^10 points (a 1024-point row is one wave) and columns of 64 points, or 128
+    // at N = 2^17, whose tiles have row runs of 512 and 256 bytes
+    p->logN1 = o.log2_n1 == 0 ? (p->logN <= 12 ? 0 : std::max(6u, p->logN - 10)) : (o.log2_n1 < 0 ? 0 : (uint32_t)o.log2_n1);
     if (!nttk::shape32_supported(p->logN, p->logN1))
       return fail(NTT_ERR_UNSUPPORTED, "no 32-bit kernels for this (N, N1) combination");
   } else if (stage_path) {
@@ -394,11 +403,16 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
   std::vector<uint64_t> mu(L), psis(L);
   std::vector<uint32_t> bits(L);
   std::vector<int> bad(L, 0);
-  // 32-bit tables: {w, floor(w 2^32 / q)} per entry, packed as one uint64 (w in the low half)
-  std::vector<uint64_t> tw32_f(w32 ? L * NN : 0), tw32_i(w32 ? L * NN : 0), scale32(w32 ? 2 * (size_t)L : 0),
-      mu64(w32 ? L : 0);
+  // 32-bit tables: the centred word w 2^32 mod q per entry
+  std::vector<int32_t> tw32_f(w32 ? L * NN : 0), tw32_i(w32 ? L * NN : 0), scale32(w32 ? 2 * (size_t)L : 0),
+      scale32_mul(w32 ? 2 * (size_t)L : 0);
+  std::vector<uint64_t> mu64(w32 ? L : 0);
   std::vector<uint32_t> q32(w32 ? L : 0);
-  auto pack32 = [](uint64_t w, uint64_t q) { return w | ((uint64_t)(((nttp::u128)w << 32) / q) << 32); };
+  std::vector<nttk::Prime32> primes32(w32 ? L : 0);
+  auto word32 = [](uint64_t w, uint64_t q) {
+    const uint64_t v = (w << 32) % q;
+    return (int32_t)(v > q / 2 ? (int64_t)v - (int64_t)q : (int64_t)v);
+  };
 
   auto work = [&](uint32_t l0, uint32_t l1) {
     std::vector<uint64_t> pw(NN), pwi(NN);
@@ -430,8 +444,8 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
         tf[i] = entry(pw[e]);
         ti[i] = entry(pwi[e]);
         if (w32) {
-          tw32_f[l * NN + i] = pack32(pw[e], q);
-          tw32_i[l * NN + i] = pack32(pwi[e], q);
+          tw32_f[l * NN + i] = word32(pw[e], q);
+          tw32_i[l * NN + i] = word32(pwi[e], q);
         }
       }
       for (size_t k = 0; k < B; ++k) {
@@ -455,8 +469,14 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
       bits[l] = s;
       mu[l] = (uint64_t)(((nttp::u128)1 << (2 * s)) / q);
       if (w32) {
-        scale32[2 * l] = pack32(n_inv, q);
-        scale32[2 * l + 1] = pack32(w1n, q);
+        const uint64_t c32 = ((uint64_t)1 << 32) % q;   // products leave a factor 2^-32
+        scale32[2 * l] = word32(n_inv, q);
+        scale32[2 * l + 1] = word32(w1n, q);
+        scale32_mul[2 * l] = word32(nttp::mulmod(n_inv, c32, q), q);
+        scale32_mul[2 * l + 1] = word32(nttp::mulmod(w1n, c32, q), q);
+        uint32_t inv = 1;   // q^-1 mod 2^32 by Newton's iteration
+        for (int k = 0; k < 5; ++k) inv *= 2 - (uint32_t)q * inv;
+        primes32[l] = {(uint32_t)q, 0u - inv};
         q32[l] = (uint32_t)q;
         mu64[l] = (uint64_t)((((nttp::u128)1) << 64) / q);
       }
@@ -499,16 +519,12 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
   }
   if (hipGetDevice(&p->device) != hipSuccess) return fail(NTT_ERR_HIP, "hipGetDevice failed");
   hipError_t e;
-  {
-    uint64_t* f = nullptr;
-    uint64_t* i = nullptr;
-    uint64_t* sc = nullptr;
-    if ((e = upload(&f, tw32_f)) != hipSuccess || (p->d_tw32_fwd = f, (e = upload(&i, tw32_i)) != hipSuccess) ||
-        (p->d_tw32_inv = i, (e = upload(&sc, scale32)) != hipSuccess) ||
-        (p->d_scale32 = sc, (e = upload(&p->d_q32, q32)) != hipSuccess) || (e = upload(&p->d_mu64, mu64)) != hipSuccess) {
-      if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of plan tables failed");
-      return hip_fail(e, "uploading plan tables");
-    }
+  if ((e = upload(&p->d_tw32_fwd, tw32_f)) != hipSuccess || (e = upload(&p->d_tw32_inv, tw32_i)) != hipSuccess ||
+      (e = upload(&p->d_scale32, scale32)) != hipSuccess || (e = upload(&p->d_scale32_mul, scale32_mul)) != hipSuccess ||
+      (e = upload(&p->d_primes32, primes32)) != hipSuccess || (e = upload(&p->d_q32, q32)) != hipSuccess ||
+      (e = upload(&p->d_mu64, mu64)) != hipSuccess) {
+    if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of plan tables failed");
+    return hip_fail(e, "uploading plan tables");
   }
   if ((e = upload(&p->d_q, p->primes)) != hipSuccess || (e = upload(&p->d_mc, mod_consts)) != hipSuccess ||
       (e = upload(&p->d_tw_fwd, tw_fwd)) != hipSuccess ||
@@ -1417,8 +1433,7 @@ ntt_status ntt_forward_u32(ntt_plan_t plan, uint32_t* d_data, uint32_t n_polys, 
     if (ntt_status s = check_data_words(plan, d_data, n_polys, 32)) return s;
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
-    const hipError_t e = nttk::launch_transform32(d_data, plan->d_tw32_fwd, plan->d_scale32, plan->d_q32,
-                                                  (uint64_t)n_polys * plan->L, plan->L, plan->logN, plan->logN1, false,
+    const hipError_t e = nttk::launch_transform32(plan->plan32(), d_data, n_polys, false,
                                                   static_cast<hipStream_t>(stream));
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_forward_u32 launch");
   } catch (...) {
@@ -1431,8 +1446,7 @@ ntt_status ntt_inverse_u32(ntt_plan_t plan, uint32_t* d_data, uint32_t n_polys, 
     if (ntt_status s = check_data_words(plan, d_data, n_polys, 32)) return s;
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
-    const hipError_t e = nttk::launch_transform32(d_data, plan->d_tw32_inv, plan->d_scale32, plan->d_q32,
-                                                  (uint64_t)n_polys * plan->L, plan->L, plan->logN, plan->logN1, true,
+    const hipError_t e = nttk::launch_transform32(plan->plan32(), d_data, n_polys, true,
                                                   static_cast<hipStream_t>(stream));
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_inverse_u32 launch");
   } catch (...) {
@@ -1470,9 +1484,13 @@ ntt_status ntt_polymul_negacyclic_u32(ntt_plan_t plan, const uint32_t* d_a, cons
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t bytes = (size_t)n_polys * plan->L * plan->N * sizeof(uint32_t);
+    hipError_t e;
+    if (!product_needs_scratch(plan)) {
+      e = nttk::launch_product32(plan->plan32(), d_a, d_b, d_c, n_polys, nullptr, st);
+      return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_polymul_negacyclic_u32 launch");
+    }
     ntt_plan_s::StreamScratch* sc = plan->scratch_for(st);
     std::lock_guard<std::mutex> lk(sc->mu);
-    hipError_t e;
     if (!sc->ev && (e = hipEventCreateWithFlags(&sc->ev, hipEventDisableTiming)) != hipSuccess) {
       sc->ev = nullptr;
       return hip_fail(e, "hipEventCreate");
@@ -1488,18 +1506,8 @@ ntt_status ntt_polymul_negacyclic_u32(ntt_plan_t plan, const uint32_t* d_a, cons
                                         : hip_fail(e, "scratch allocation");
       sc->bytes = bytes;
     }
-    uint32_t* tmp = reinterpret_cast<uint32_t*>(sc->buf);
-    const uint64_t n_vec = (uint64_t)n_polys * plan->L;
-    if ((d_c != d_a && (e = hipMemcpyAsync(d_c, d_a, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess) ||
-        (e = hipMemcpyAsync(tmp, d_b, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess ||
-        (e = nttk::launch_transform32(d_c, plan->d_tw32_fwd, plan->d_scale32, plan->d_q32, n_vec, plan->L, plan->logN,
-                                      plan->logN1, false, st)) != hipSuccess ||
-        (e = nttk::launch_transform32(tmp, plan->d_tw32_fwd, plan->d_scale32, plan->d_q32, n_vec, plan->L, plan->logN,
-                                      plan->logN1, false, st)) != hipSuccess ||
-        (e = nttk::launch_pointwise32(d_c, tmp, d_c, plan->d_q32, plan->d_mu64, n_vec * plan->N, plan->logN, plan->L,
-                                      st)) != hipSuccess ||
-        (e = nttk::launch_transform32(d_c, plan->d_tw32_inv, plan->d_scale32, plan->d_q32, n_vec, plan->L, plan->logN,
-                                      plan->logN1, true, st)) != hipSuccess)
+    if ((e = nttk::launch_product32(plan->plan32(), d_a, d_b, d_c, n_polys, reinterpret_cast<uint32_t*>(sc->buf), st)) !=
+        hipSuccess)
       return hip_fail(e, "ntt_polymul_negacyclic_u32 launch");
     if ((e = hipEventRecord(sc->ev, st)) != hipSuccess) return hip_fail(e, "recording scratch event");
     sc->pending = true;

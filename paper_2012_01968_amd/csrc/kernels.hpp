@@ -44,10 +44,21 @@ uint32_t stage_group_count(uint32_t logN, int log2_radix);
 hipError_t launch_stage_group(const PassArgs& a, int log2_radix, bool inverse, uint32_t g, hipStream_t st);
 hipError_t launch_stage_groups(const PassArgs& a, int log2_radix, bool inverse, hipStream_t st);
 
-// 32-bit words (kernels32.hip): primes below 2^30, tables of {w, floor(w 2^32 / q)} pairs.
+// 32-bit words (kernels32.hip): primes below 2^30, tables of the centred words w 2^32 mod q.
+struct Prime32 {
+  uint32_t q, nqi;          // q and -q^-1 mod 2^32
+};
+struct Plan32 {
+  const int32_t *tw_fwd, *tw_inv;        // [L][N]
+  const int32_t *scale, *scale_mul;      // [L][2]: {1/N}, {Psi_inv[1]/N}; of products: times 2^32
+  const Prime32* primes;                 // [L]
+  uint32_t L, logN, logN1;
+};
 bool shape32_supported(uint32_t logN, uint32_t logN1);
-hipError_t launch_transform32(uint32_t* data, const void* tw, const void* scale, const uint32_t* q, uint64_t n_vec,
-                              uint32_t L, uint32_t logN, uint32_t logN1, bool inverse, hipStream_t st);
+hipError_t launch_transform32(const Plan32& p, uint32_t* data, uint32_t n_polys, bool inverse, hipStream_t st);
+// c = a * b (negacyclic); `tmp` holds b's column pass (n_polys*L*N words; unused when logN1 = 0).
+hipError_t launch_product32(const Plan32& p, const uint32_t* a, const uint32_t* b, uint32_t* c, uint32_t n_polys,
+                            uint32_t* tmp, hipStream_t st);
 hipError_t launch_pointwise32(const uint32_t* A, const uint32_t* B, uint32_t* C, const uint32_t* qs,
                               const uint64_t* mus, uint64_t n, uint32_t logN, uint32_t L, hipStream_t st);
 

@@ -40,3 +40,25 @@ def test_product(logN, log2_n1, L, P, bits, ots, r1):
         assert np.array_equal(da.cpu().numpy().view(np.uint64), want)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("logN,log2_n1,L,P", [(1, 0, 3, 1), (5, 0, 5, 3), (12, 0, 1, 3), (10, 5, 3, 1), (13, 0, 1, 1),
+                                              (17, 5, 1, 3), (17, 0, 1, 1), (16, 10, 2, 1)])
+def test_product_word32(logN, log2_n1, L, P):
+    """The same on 32-bit words, at the narrow and the wide column tiles and rows of 2 to 4096 points."""
+    N = 1 << logN
+    primes = synth.gen_primes(7800 + logN + L, N, 30, L)
+    plan = ntt.ntt_plan_create(N, primes, word_bits=32, log2_n1=log2_n1)
+    try:
+        a, b = synth.residue_batch(7801, primes, N, P), synth.residue_batch(7802, primes, N, P)
+        a[0, :, 0] = np.array(primes, dtype=np.uint64) - np.uint64(1)
+        want = oracle.polymul(a, b, primes, oracle.roots(primes, N)).astype(np.int32)
+        da, db = (torch.from_numpy(v.astype(np.int32)).to("cuda") for v in (a, b))
+        c = torch.empty_like(da)
+        ntt.ntt_polymul_negacyclic_u32(plan, da, db, c)
+        assert np.array_equal(c.cpu().numpy(), want)
+        assert np.array_equal(db.cpu().numpy(), b.astype(np.int32)) and np.array_equal(da.cpu().numpy(), a.astype(np.int32))
+        ntt.ntt_polymul_negacyclic_u32(plan, da, db, da)      # c may alias a
+        assert np.array_equal(da.cpu().numpy(), want)
+    finally:
+        plan.destroy()

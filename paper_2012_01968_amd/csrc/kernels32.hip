@@ -260,12 +260,11 @@ __global__ __launch_bounds__(Row32<LOGM>::NT) void row32_kernel(Args32 a) {
   int32_t x[S::R], w[S::R];
   if constexpr (MODE != kRow32Inverse) {
     auto forward = [&](const uint32_t* in) {
-#pragma unroll
-      for (int u = 0; u < S::R; ++u) x[u] = 0;
-      if (valid) load_row32<C>(x, in + off, t);
+      load_row32<C>(x, in + off, t);   // padding rows read row 0 and store nothing
       static_for<0, S::K>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         load_twiddles32<LOGM, kLR32, k>(w, t, base, tab);   // before the exchange, which they overlap
+        loads_issued();
         if constexpr (k > 0) exchange32<C, (k > 0 ? k - 1 : 0), k>(x, l, t);
         ct32_step<LOGM, kLR32, k, ONEP>(x, w, p);
       });
@@ -291,20 +290,16 @@ __global__ __launch_bounds__(Row32<LOGM>::NT) void row32_kernel(Args32 a) {
     }
   } else {
     const gu32* in = (const gu32*)(out) + S::template idx<S::K - 1>(t, 0);
+    if constexpr (S::R % 4 == 0 && S::K > 1) {   // the last step's 2^LR elements are consecutive
+      typedef Vec32<4>::type vec4;
 #pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = 0;
-    if (valid) {
-      if constexpr (S::R % 4 == 0 && S::K > 1) {   // the last step's 2^LR elements are consecutive
-        typedef Vec32<4>::type vec4;
+      for (int u = 0; u < S::R; u += 4) {
+        const vec4 q4 = *(const __attribute__((address_space(1))) vec4*)(in + u);
 #pragma unroll
-        for (int u = 0; u < S::R; u += 4) {
-          const vec4 q4 = *(const __attribute__((address_space(1))) vec4*)(in + u);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) x[u + j] = q4[j];
-        }
-      } else {
-        load_row32<C>(x, out, t);
+        for (int j = 0; j < 4; ++j) x[u + j] = q4[j];
       }
+    } else {
+      load_row32<C>(x, out, t);
     }
   }
   if constexpr (MODE != kRow32Forward) {
@@ -316,6 +311,7 @@ __global__ __launch_bounds__(Row32<LOGM>::NT) void row32_kernel(Args32 a) {
     static_for_down<S::K, 0>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       load_twiddles32<LOGM, kLR32, k>(w, t, base, tab);
+      loads_issued();
       if constexpr (k < S::K - 1) exchange32<C, k + 1, k>(x, l, t);
       gs32_step<LOGM, kLR32, k, ONEP>(x, w, p, sc0, sc1);
     });

@@ -123,7 +123,10 @@ struct RowRef {
   const gu64* keyp; // the row of the key vector at the same position (key-product launches)
   uint32_t limb;    // its prime
   uint32_t base;    // N1 + (row within its vector): the row's twiddle base
-  bool valid;       // false for padding rows
+  bool valid;       // false for padding rows: their pointers are row 0's, which they read and never store
+                    // (so that the transform is one basic block: with the loads or the product under a
+                    // branch, the compiler lost sight of 32-bit operands and took four times as many
+                    // instructions for 48 multiply-adds of the 256-point key-product row)
 };
 
 // Row v of this workgroup's tile.  When V divides N1 (every split launch with at least V
@@ -228,13 +231,8 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void fwd_row_kernel(P
   uint64_t* l = lds + v * C::PITCH;
 
   uint64_t x[S::R];
-  if (valid) {
 #pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = rr.srcp[S::template idx<0>(t, u)];
-  } else {
-#pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = 0;
-  }
+  for (int u = 0; u < S::R; ++u) x[u] = rr.srcp[S::template idx<0>(t, u)];
 
   static_for<0, S::K>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
@@ -245,6 +243,7 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void fwd_row_kernel(P
       if constexpr (k == 0 && C::T >= 64)
         load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, 0u, __builtin_amdgcn_readfirstlane(base), tabu, ot);
       else load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, t, base, tabfn, ot);
+      loads_issued();
     }
     if constexpr (k > 0) {
 #pragma unroll
@@ -335,13 +334,8 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void inv_row_kernel(P
   // wave's loads still cover whole lines across its 4 instructions, and no LDS exchange
   // precedes the first step
   uint64_t x[S::R];
-  if (valid) {
 #pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = rowp[S::template idx<S::K - 1>(t, u)];
-  } else {
-#pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = 0;
-  }
+  for (int u = 0; u < S::R; ++u) x[u] = rowp[S::template idx<S::K - 1>(t, u)];
 
   static_for_down<S::K, 0>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
@@ -352,6 +346,7 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void inv_row_kernel(P
       if constexpr (k == 0 && C::T >= 64)
         load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, 0u, __builtin_amdgcn_readfirstlane(base), tabu, ot);
       else load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, t, base, tabfn, ot);
+      loads_issued();
     }
     if constexpr (k < S::K - 1) {
 #pragma unroll
@@ -441,21 +436,12 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
   uint64_t* l = lds + v * C::PITCH;
   uint64_t* l2 = l + (BUFS - 1) * C::V * C::PITCH;   // the second operand's buffer
 
-  uint64_t x[S::R], y[PAIR ? S::R : 1];
-  if (valid) {
+  uint64_t x[S::R], f[S::R];   // f: the second operand, or the key
 #pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = rr.srcp[S::template idx<0>(t, u)];
-    if constexpr (PAIR) {
+  for (int u = 0; u < S::R; ++u) x[u] = rr.srcp[S::template idx<0>(t, u)];
+  if constexpr (PAIR) {
 #pragma unroll
-      for (int u = 0; u < S::R; ++u) y[u] = rr.keyp[S::template idx<0>(t, u)];
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < S::R; ++u) x[u] = 0;
-    if constexpr (PAIR) {
-#pragma unroll
-      for (int u = 0; u < S::R; ++u) y[u] = 0;
-    }
+    for (int u = 0; u < S::R; ++u) f[u] = rr.keyp[S::template idx<0>(t, u)];
   }
   static_for<0, S::K>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
@@ -464,12 +450,17 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
       load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, 0u, __builtin_amdgcn_readfirstlane(base), tabuf, otf);
     else
       load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, t, base, tabfnf, otf);
+    if constexpr (!PAIR && k == S::K - 1) {
+#pragma unroll
+      for (int u = 0; u < S::R; ++u) f[u] = rr.keyp[S::template idx<S::K - 1>(t, u)];
+    }
+    loads_issued();
     if constexpr (k > 0) {
 #pragma unroll
       for (int u = 0; u < S::R; ++u) l[C::at(S::template idx<k - 1>(t, u))] = x[u];
       if constexpr (PAIR && BUFS == 2) {
 #pragma unroll
-        for (int u = 0; u < S::R; ++u) l2[C::at(S::template idx<k - 1>(t, u))] = y[u];
+        for (int u = 0; u < S::R; ++u) l2[C::at(S::template idx<k - 1>(t, u))] = f[u];
       }
       row_sync<C::T>();
 #pragma unroll
@@ -478,33 +469,26 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
         if constexpr (BUFS == 1) {   // the same slots again, once every lane has read the first operand's
           row_sync<C::T>();
 #pragma unroll
-          for (int u = 0; u < S::R; ++u) l2[C::at(S::template idx<k - 1>(t, u))] = y[u];
+          for (int u = 0; u < S::R; ++u) l2[C::at(S::template idx<k - 1>(t, u))] = f[u];
           row_sync<C::T>();
         }
 #pragma unroll
-        for (int u = 0; u < S::R; ++u) y[u] = l2[C::at(S::template idx<k>(t, u))];
+        for (int u = 0; u < S::R; ++u) f[u] = l2[C::at(S::template idx<k>(t, u))];
       }
     }
     constexpr int IN = SCALE0 ? kCtCanon : kCtLazy;
     ct_step<FAST, LOGM, C::LR, k, OTS, IN>(x, t, base, tabfnf, otf, md, pre);
-    if constexpr (PAIR) ct_step<FAST, LOGM, C::LR, k, OTS, IN>(y, t, base, tabfnf, otf, md, pre);
+    if constexpr (PAIR) ct_step<FAST, LOGM, C::LR, k, OTS, IN>(f, t, base, tabfnf, otf, md, pre);
   });
   // times the second factor at the same positions
-  if (valid) {
-    uint64_t mu = 0;
-    uint32_t bits = 0;
-    if constexpr (!FAST) {
-      mu = ((cu64*)af.mu)[limb];
-      bits = ((const __attribute__((address_space(4))) uint32_t*)af.bits)[limb];
-    }
-#pragma unroll
-    for (int u = 0; u < S::R; ++u) {
-      uint64_t f;
-      if constexpr (PAIR) f = y[u];
-      else f = rr.keyp[S::template idx<S::K - 1>(t, u)];
-      x[u] = ntt_domain_product<FAST, PAIR>(x[u], f, md, mu, bits);
-    }
+  uint64_t mu = 0;
+  uint32_t bits = 0;
+  if constexpr (!FAST) {
+    mu = ((cu64*)af.mu)[limb];
+    bits = ((const __attribute__((address_space(4))) uint32_t*)af.bits)[limb];
   }
+#pragma unroll
+  for (int u = 0; u < S::R; ++u) x[u] = ntt_domain_product<FAST, PAIR>(x[u], f[u], md, mu, bits);
   static_for_down<S::K, 0>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     PreTw<S::R> pre;
@@ -512,6 +496,7 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
       load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, 0u, __builtin_amdgcn_readfirstlane(base), tabui, oti);
     else
       load_step_twiddles<LOGM, C::LR, k, OTS>(pre.w, pre.w2, t, base, tabfni, oti);
+    loads_issued();
     if constexpr (k < S::K - 1) {
       // the first of these writes goes to the slots this lane read in the forward half's
       // last exchange, which no other lane reads, so it needs no barrier before it
@@ -521,7 +506,7 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void mul_row_kernel(P
 #pragma unroll
       for (int u = 0; u < S::R; ++u) x[u] = l[C::at(S::template idx<k>(t, u))];
     }
-    // the product leaves values within q of 0 (padding rows skip it, but are never stored)
+    // the product leaves values within q of 0
     gs_step<FAST, LOGM, C::LR, k, OTS, SCALE0, k == S::K - 1 ? kGsCanon : kGsLazy>(x, t, base, tabfni, oti, md, sc0, sc1, pre);
   });
   if constexpr (SCALE0) {

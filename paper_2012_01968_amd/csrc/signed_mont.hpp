@@ -115,8 +115,12 @@ NTTK_HD uint64_t mont_canonical_2q(int64_t x, const MontMod& m) {
 
 // x y 2^-62 mod q for |x|, |y| <= q: two digits of x in turn.  |result| <= |x y| / 2^62 + q/2 + 2 < q.
 NTTK_HD int64_t mont_product(int64_t x, int64_t y, const MontMod& m) {
-  const int32_t x0 = (int32_t)((uint32_t)x << 1) >> 1, x1 = (int32_t)((x + (1 << 30)) >> 31);
-  const int32_t y0 = (int32_t)((uint32_t)y << 1) >> 1, y1 = (int32_t)((y + (1 << 30)) >> 31);
+  int32_t x0 = (int32_t)((uint32_t)x << 1) >> 1, x1 = (int32_t)((x + (1 << 30)) >> 31);
+  int32_t y0 = (int32_t)((uint32_t)y << 1) >> 1, y1 = (int32_t)((y + (1 << 30)) >> 31);
+  keep(x0);   // as 32-bit values: seen through, the upper digits would make 64-bit products
+  keep(x1);
+  keep(y0);
+  keep(y1);
   int64_t P = (int64_t)x0 * y0;
   const int32_t t0 = (int32_t)((uint32_t)P * m.qi2) >> 1;
   P += (int64_t)t0 * m.q0;

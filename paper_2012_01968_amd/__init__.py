@@ -195,11 +195,20 @@ class Plan:
             pass
 
 
+_int_sizes: dict = {}   # torch integer dtype -> bytes, filled as dtypes are seen
+
+
 def _addr(buf, need: int | None = None, what: str = "buffer", esize: int = 8) -> int:
     """Device address of `buf` for the C ABI.  A raw integer is passed through as given (the
     caller vouches for it).  A tensor must live on the GPU, hold integers of `esize` bytes, be
     contiguous and have at least `need` elements: anything else would reach the kernels as a
     pointer to memory they cannot address or to too few elements."""
+    try:    # the accepted case in four attribute reads; everything else is looked at below
+        if (_int_sizes[buf.dtype] == esize and buf.is_cuda and buf.is_contiguous()
+                and (need is None or buf.numel() >= need)):
+            return buf.data_ptr()
+    except (AttributeError, KeyError):
+        pass
     if buf is None:
         raise ValueError(f"{what} is None")
     if isinstance(buf, int):
@@ -212,13 +221,30 @@ def _addr(buf, need: int | None = None, what: str = "buffer", esize: int = 8) ->
         raise ValueError(f"{what} must be contiguous")
     if need is not None and buf.numel() < need:
         raise ValueError(f"{what} holds {buf.numel()} elements; the call needs {need}")
+    _int_sizes[buf.dtype] = esize
     return int(buf.data_ptr())
+
+
+def _first_current_stream() -> int:
+    """torch's current stream; from then on through the two queries below it, which take a tenth
+    of the time of building a Stream object per call (a small transform's launch takes 3 us)."""
+    global _current_stream
+    import torch
+    raw = int(torch.cuda.current_stream().cuda_stream)     # initialises the GPU state if nothing has
+    device, stream_of = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device is not None and stream_of is not None and int(stream_of(device())) == raw:
+        _current_stream = lambda: stream_of(device())  # noqa: E731
+    else:
+        _current_stream = lambda: int(torch.cuda.current_stream().cuda_stream)  # noqa: E731
+    return raw
+
+
+_current_stream = _first_current_stream
 
 
 def _stream(stream) -> int | None:
     if stream is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream) or None
+        return _current_stream() or None
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
@@ -281,13 +307,17 @@ def ntt_plan_get_info(plan: Plan) -> dict:
 
 
 def ntt_forward(plan: Plan, data, n_polys: int | None = None, stream=None) -> None:
-    n, (d,) = _batch_addrs(plan, [data], ["data"], n_polys)
-    _check(_lib.ntt_forward(plan.handle, d, n, _stream(stream)), "ntt_forward")
+    n = _polys(plan, data, n_polys)
+    status = _lib.ntt_forward(plan.handle, _addr(data, n * plan.L * plan.N, "data"), n, _stream(stream))
+    if status:
+        raise NttError(status, "ntt_forward")
 
 
 def ntt_inverse(plan: Plan, data, n_polys: int | None = None, stream=None) -> None:
-    n, (d,) = _batch_addrs(plan, [data], ["data"], n_polys)
-    _check(_lib.ntt_inverse(plan.handle, d, n, _stream(stream)), "ntt_inverse")
+    n = _polys(plan, data, n_polys)
+    status = _lib.ntt_inverse(plan.handle, _addr(data, n * plan.L * plan.N, "data"), n, _stream(stream))
+    if status:
+        raise NttError(status, "ntt_inverse")
 
 
 def ntt_forward_pass(plan: Plan, data, pass_index: int, n_polys: int | None = None, stream=None) -> None:

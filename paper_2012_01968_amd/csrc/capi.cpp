@@ -71,6 +71,30 @@ hipError_t upload(T** dst, const std::vector<T>& src) {
   return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
 }
 
+// Several small tables in one device allocation and one copy: each add() names the pointer that its
+// part sets (256-byte aligned); the caller frees the pointer that upload() returns.
+struct TablePack {
+  std::vector<char> bytes;
+  std::vector<std::pair<void**, size_t>> parts;
+  template <typename T>
+  void add(T** dst, const std::vector<T>& src) {
+    if (src.empty()) return;
+    const size_t off = (bytes.size() + 255) / 256 * 256, n = src.size() * sizeof(T);
+    bytes.resize(off + n);
+    std::memcpy(bytes.data() + off, src.data(), n);
+    parts.emplace_back(reinterpret_cast<void**>(dst), off);
+  }
+  hipError_t upload(void** base) {
+    *base = nullptr;
+    if (bytes.empty()) return hipSuccess;
+    hipError_t e = hipMalloc(base, bytes.size());
+    if (e != hipSuccess) return e;
+    if ((e = hipMemcpy(*base, bytes.data(), bytes.size(), hipMemcpyHostToDevice)) != hipSuccess) return e;
+    for (auto& p : parts) *p.first = static_cast<char*>(*base) + p.second;
+    return hipSuccess;
+  }
+};
+
 }  // namespace
 
 struct ntt_plan_s {
@@ -96,6 +120,7 @@ struct ntt_plan_s {
   bool fast = false;  // all primes below 2^60 (wider lazy ranges, estimated quotients)
   std::vector<uint64_t> primes, psis;
 
+  void* d_small = nullptr;    // the small tables' memory: d_q, d_mc, OT tables, d_scale*, d_mu, d_bits, *32
   uint64_t* d_q = nullptr;
   uint64_t* d_mc = nullptr;   // [L][8] per-prime constants of the split passes
   Tw* d_tw_fwd = nullptr;
@@ -122,6 +147,7 @@ struct ntt_plan_s {
   struct Crt {
     std::mutex mu;
     bool ready = false;
+    void* base = nullptr;           // the tables' memory
     uint32_t W = 0;                 // words of Q
     bool all_wide = false;          // every prime has at least 47 bits
     int8_t* dec = nullptr;          // digit matrix of the decomposition
@@ -171,10 +197,7 @@ struct ntt_plan_s {
       (void)hipEventSynchronize(fused_ev);
       (void)hipEventDestroy(fused_ev);
     }
-    void* ptrs[] = {d_q, d_mc, d_tw_fwd, d_tw_inv, d_ot_lo_fwd, d_ot_hi_fwd, d_ot_lo_inv, d_ot_hi_inv,
-                    d_scale, d_scale_mul, d_mu, d_bits, d_ctr, d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul,
-                    d_primes32, d_q32, d_mu64,
-                    crt.dec, crt.dec_off, crt.dec_primes, crt.rec, crt.rec_primes, crt.Q};
+    void* ptrs[] = {d_small, d_tw_fwd, d_tw_inv, d_ctr, d_tw32_fwd, d_tw32_inv, crt.base};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
   }
@@ -519,19 +542,25 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
   }
   if (hipGetDevice(&p->device) != hipSuccess) return fail(NTT_ERR_HIP, "hipGetDevice failed");
   hipError_t e;
-  if ((e = upload(&p->d_tw32_fwd, tw32_f)) != hipSuccess || (e = upload(&p->d_tw32_inv, tw32_i)) != hipSuccess ||
-      (e = upload(&p->d_scale32, scale32)) != hipSuccess || (e = upload(&p->d_scale32_mul, scale32_mul)) != hipSuccess ||
-      (e = upload(&p->d_primes32, primes32)) != hipSuccess || (e = upload(&p->d_q32, q32)) != hipSuccess ||
-      (e = upload(&p->d_mu64, mu64)) != hipSuccess) {
-    if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of plan tables failed");
-    return hip_fail(e, "uploading plan tables");
-  }
-  if ((e = upload(&p->d_q, p->primes)) != hipSuccess || (e = upload(&p->d_mc, mod_consts)) != hipSuccess ||
-      (e = upload(&p->d_tw_fwd, tw_fwd)) != hipSuccess ||
-      (e = upload(&p->d_tw_inv, tw_inv)) != hipSuccess || (e = upload(&p->d_ot_lo_fwd, ot_lo_f)) != hipSuccess ||
-      (e = upload(&p->d_ot_hi_fwd, ot_hi_f)) != hipSuccess || (e = upload(&p->d_ot_lo_inv, ot_lo_i)) != hipSuccess ||
-      (e = upload(&p->d_ot_hi_inv, ot_hi_i)) != hipSuccess || (e = upload(&p->d_scale, scale)) != hipSuccess || (e = upload(&p->d_scale_mul, scale_mul)) != hipSuccess ||
-      (e = upload(&p->d_mu, mu)) != hipSuccess || (e = upload(&p->d_bits, bits)) != hipSuccess) {
+  TablePack pack;
+  pack.add(&p->d_q, p->primes);
+  pack.add(&p->d_mc, mod_consts);
+  pack.add(&p->d_ot_lo_fwd, ot_lo_f);
+  pack.add(&p->d_ot_hi_fwd, ot_hi_f);
+  pack.add(&p->d_ot_lo_inv, ot_lo_i);
+  pack.add(&p->d_ot_hi_inv, ot_hi_i);
+  pack.add(&p->d_scale, scale);
+  pack.add(&p->d_scale_mul, scale_mul);
+  pack.add(&p->d_mu, mu);
+  pack.add(&p->d_bits, bits);
+  pack.add(&p->d_scale32, scale32);
+  pack.add(&p->d_scale32_mul, scale32_mul);
+  pack.add(&p->d_primes32, primes32);
+  pack.add(&p->d_q32, q32);
+  pack.add(&p->d_mu64, mu64);
+  if ((e = pack.upload(&p->d_small)) != hipSuccess || (e = upload(&p->d_tw_fwd, tw_fwd)) != hipSuccess ||
+      (e = upload(&p->d_tw_inv, tw_inv)) != hipSuccess || (e = upload(&p->d_tw32_fwd, tw32_f)) != hipSuccess ||
+      (e = upload(&p->d_tw32_inv, tw32_i)) != hipSuccess) {
     if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of plan tables failed");
     return hip_fail(e, "uploading plan tables");
   }
@@ -1550,10 +1579,14 @@ static ntt_status crt_prepare(ntt_plan_t plan) {
   DeviceGuard g(plan->device);
   if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
   hipError_t e;
-  if ((e = upload(&plan->crt.dec, dec.digits)) != hipSuccess ||
-      (e = upload(&plan->crt.dec_off, dec.offsets)) != hipSuccess ||
-      (e = upload(&plan->crt.dec_primes, dp)) != hipSuccess || (e = upload(&plan->crt.rec, rec)) != hipSuccess ||
-      (e = upload(&plan->crt.rec_primes, rp)) != hipSuccess || (e = upload(&plan->crt.Q, t.Q)) != hipSuccess) {
+  TablePack pack;
+  pack.add(&plan->crt.dec, dec.digits);
+  pack.add(&plan->crt.dec_off, dec.offsets);
+  pack.add(&plan->crt.dec_primes, dp);
+  pack.add(&plan->crt.rec, rec);
+  pack.add(&plan->crt.rec_primes, rp);
+  pack.add(&plan->crt.Q, t.Q);
+  if ((e = pack.upload(&plan->crt.base)) != hipSuccess) {
     if (e == hipErrorOutOfMemory) return fail(NTT_ERR_NOMEM, "device allocation of conversion tables failed");
     return hip_fail(e, "uploading conversion tables");
   }

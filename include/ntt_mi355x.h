@@ -169,8 +169,8 @@ ntt_status ntt_plan_get_info(ntt_plan_t plan, uint32_t* N, uint32_t* L, uint32_t
                              int32_t* twiddle_mode, int32_t* ot_stages, int32_t* kernel_path);
 
 /* The tile shape the plan was created with (r1, wg_size, col_width of ntt_plan_opts; 0 where
- * the built-in default applies: 8 values per lane, 128-lane row workgroups, and 64 columns
- * per column tile where N2 holds them, else 16).  Any pointer may be NULL. */
+ * the built-in default applies: 8 values per lane and 128-lane row workgroups, or 4 and 64 for
+ * small launches, and 64 columns per column tile where N2 holds them, else 16).  Any pointer may be NULL. */
 ntt_status ntt_plan_get_tiles(ntt_plan_t plan, int32_t* r1, int32_t* wg_size, int32_t* col_width);
 
 /* In-place forward NTT of every vector of d_data ([n_polys][L][N] uint64, device).

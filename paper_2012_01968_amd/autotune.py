@@ -104,7 +104,7 @@ def tile_candidates(N: int, opts: dict) -> list[dict]:
         return [dict(opts)]
     n1 = opts.get("log2_n1", 0)
     if n1 == 0:
-        n1 = 0 if logN <= 12 else logN // 2
+        n1 = 0 if logN <= 12 else {13: 5, 17: 8}.get(logN, 6)   # the library's automatic split
     n1 = max(n1, 0)
     logm = logN - n1
     out, seen = [], set()

@@ -107,6 +107,7 @@ struct ntt_plan_s {
   int32_t log2_radix = 0;                 // RADIX2 / REGISTER paths: stages per launch
   int32_t word_bits = 64;                 // residue word: 64 (uint64_t) or 32 (uint32_t, q < 2^30)
   uint32_t row_lr = 0, row_nth = 0, col_w = 0;   // split-pass tile shape (0 = built-in default)
+  bool auto_split = false;                // the split and the tile shape are the library's choice
   uint32_t debug = 0;                     // split-pass debug modes (NTT_DEBUG at creation)
   uint32_t fused_lag = 4;                 // vectors an XCD queue runs pass 1 ahead of pass 2
   uint32_t fused_grid = 1024;             // persistent workgroups (4 per CU)
@@ -231,6 +232,20 @@ struct ntt_plan_s {
   nttk::Plan32 plan32() const {
     return nttk::Plan32{d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul, d_primes32, L, logN, logN1};
   }
+  // log2 N1 of a launch over n_vec vectors of an automatic plan (the tables serve every split):
+  //  * N = 2^13 takes one pass (1024 lanes and 68 KB of LDS per vector) where the vectors fill the
+  //    chip: forward + inverse of 240 vectors 28 us against 33 us, products 31 against 41; 7 vectors
+  //    22.6 against 13.1.  (Between them, 120 vectors take the same time either way.)
+  //  * N = 2^15 and 2^16 take columns of 2^7 points up to 2^21 residues, where the shorter rows' chain
+  //    of stages counts: 39 vectors of 2^15 28.6 us against 29.3 (62-bit primes 33.4 against 35.2), 21 of
+  //    2^16 32.2 against 33.7 (37.5 against 39.7); above, 90 vectors of 2^15 52.5 against 50.5 with 2^6.
+  static constexpr uint64_t kOnePassVectors = 192;
+  static constexpr uint64_t kSmallLaunch = 1u << 21;
+  uint32_t split_for(uint64_t n_vec) const {
+    if (auto_split && logN == 13 && n_vec >= kOnePassVectors) return 0;
+    if (auto_split && (logN == 15 || logN == 16) && (n_vec << logN) <= kSmallLaunch) return 7;
+    return logN1;
+  }
   int active_ot() const { return twiddle_mode == NTT_TWIDDLE_OT ? ot_stages : 0; }
   // the paths whose data goes back to global memory after every group of stages
   bool stage_path() const { return kernel_path == NTT_PATH_RADIX2 || kernel_path == NTT_PATH_REGISTER; }
@@ -353,7 +368,12 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
       return fail(NTT_ERR_ARG, "the register path takes log2_radix 2..5 (1 is NTT_PATH_RADIX2)");
   } else {
     if (o.log2_n1 == 0) {
-      p->logN1 = p->logN <= 12 ? 0 : p->logN / 2;
+      // One pass up to 2^12.  Above, columns of 2^5 or 2^6 points up to N = 2^16, whose tiles have row
+      // runs of 512 bytes, and of 2^8 at 2^17 (forward + inverse, us, at log2 N / 2 and here: 2^14 x 480
+      // vectors 109 / 105, 2^15 x 90 54.8 / 51.3, 2^16 x 360 340 / 326; at 2^17 x 120, 2^6 takes 229.7 and
+      // 2^8 228.2, a product 304 and 297).  The fused path is built for log2 N / 2.
+      p->logN1 = p->logN <= 12 ? 0 : o.kernel_path == NTT_PATH_FUSED ? p->logN / 2
+                 : p->logN == 13 ? 5 : p->logN == 17 ? 8 : 6;
     } else if (o.log2_n1 < 0) {
       p->logN1 = 0;
     } else {
@@ -385,6 +405,9 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
     if (!nttk::tiles_supported(p->logN, p->logN1, p->row_lr, p->row_nth, p->col_w))
       return fail(NTT_ERR_UNSUPPORTED, "col_width needs a column pass with at least that many columns");
   }
+
+  p->auto_split = !w32 && !stage_path && o.log2_n1 == 0 && o.kernel_path != NTT_PATH_FUSED && !o.r1 && !o.wg_size &&
+                  !o.col_width;
 
   // ---- primes
   p->primes.assign(primes, primes + L);
@@ -613,7 +636,9 @@ static hipError_t enqueue_direction(ntt_plan_t plan, const PassArgs& a, bool inv
 static hipError_t transform_brv(ntt_plan_t plan, uint64_t* data, uint32_t n_polys, bool inverse, hipStream_t st,
                                 uint32_t limbs) {
   if ((limbs == 0 || limbs == plan->L) && plan->fused_for(n_polys)) return launch_fused(plan, data, n_polys, inverse, st);
-  return enqueue_direction(plan, plan->args(data, n_polys, inverse, limbs), inverse, st);
+  PassArgs a = plan->args(data, n_polys, inverse, limbs);
+  a.logN1 = plan->split_for(a.n_vec);
+  return enqueue_direction(plan, a, inverse, st);
 }
 
 // A transform as the caller sees it: natural-order plans permute the NTT-domain slots after
@@ -669,7 +694,9 @@ static ntt_status check_product(ntt_plan_t plan, const uint64_t* d_a, const uint
 
 // Whether a product needs scratch of the operands' size: a single-pass split plan reads both
 // operands, multiplies and writes c in one launch.
-static bool product_needs_scratch(ntt_plan_t plan) { return plan->kernel_path != NTT_PATH_SPLIT || plan->logN1 != 0; }
+static bool product_needs_scratch(ntt_plan_t plan, uint32_t n_polys) {
+  return plan->kernel_path != NTT_PATH_SPLIT || plan->split_for((uint64_t)n_polys * plan->L) != 0;
+}
 
 // The launches of c = a * b with b's transform placed in `tmp` (n_polys*L*N words of device memory
 // that nothing else uses until they complete).  Split plans: the forward column passes of both
@@ -685,7 +712,8 @@ static hipError_t polymul_enqueue(ntt_plan_t plan, const uint64_t* d_a, const ui
     PassArgs rows = plan->args(d_c, n_polys, false);
     PassArgs inv = plan->args(d_c, n_polys, true);
     inv.scale = plan->d_scale_mul;
-    if (plan->logN1) {
+    rows.logN1 = inv.logN1 = plan->split_for(rows.n_vec);
+    if (rows.logN1) {
       PassArgs cols = rows;
       cols.src = d_a;
       cols.data2 = tmp;
@@ -787,6 +815,7 @@ struct ntt_batch_s {
     a.n_vec = n;
     a.P = 1;
     a.L = g.plan->L;
+    a.logN1 = g.plan->split_for(n);
     return a;
   }
 
@@ -813,7 +842,7 @@ struct ntt_batch_s {
   // Phase `phase` (0 forward, 1 key products, 2 inverse) of one plan's vectors.
   hipError_t group_phase(const Group& g, int phase, hipStream_t st) const {
     const int ot = g.plan->active_ot();
-    const bool split = g.plan->logN1 != 0;
+    const bool split = g.plan->split_for(g.n_full) != 0;
     hipError_t e = hipSuccess;
     if (phase == 1) {
       if (g.n_key &&
@@ -1222,7 +1251,7 @@ ntt_status ntt_polymul_negacyclic(ntt_plan_t plan, const uint64_t* d_a, const ui
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t bytes = (size_t)n_polys * plan->L * plan->N * sizeof(uint64_t);
     hipError_t e;
-    if (!product_needs_scratch(plan)) {
+    if (!product_needs_scratch(plan, n_polys)) {
       e = polymul_enqueue(plan, d_a, d_b, d_c, n_polys, nullptr, st);
       return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_polymul_negacyclic launch");
     }
@@ -1514,7 +1543,7 @@ ntt_status ntt_polymul_negacyclic_u32(ntt_plan_t plan, const uint32_t* d_a, cons
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t bytes = (size_t)n_polys * plan->L * plan->N * sizeof(uint32_t);
     hipError_t e;
-    if (!product_needs_scratch(plan)) {
+    if (!product_needs_scratch(plan, n_polys)) {
       e = nttk::launch_product32(plan->plan32(), d_a, d_b, d_c, n_polys, nullptr, st);
       return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_polymul_negacyclic_u32 launch");
     }

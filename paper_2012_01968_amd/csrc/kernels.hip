@@ -19,7 +19,7 @@ extern template hipError_t mul_rows<true>(const PassArgs&, const PassArgs&, int,
 extern template hipError_t mul_rows<false>(const PassArgs&, const PassArgs&, int, hipStream_t);
 
 // ------------------------------------------------------------------------ element-wise
-// c = a * b mod q_l over a [n_vec][N] batch, two elements per lane per iteration.
+// c = a * b mod q_l over a [n_vec][N] batch, two elements per lane and access.
 __global__ __launch_bounds__(256) void pointwise_kernel(const uint64_t* __restrict__ A, const uint64_t* __restrict__ B,
                                                         uint64_t* __restrict__ Cc, const uint64_t* __restrict__ qs,
                                                         const uint64_t* __restrict__ mus,
@@ -27,12 +27,11 @@ __global__ __launch_bounds__(256) void pointwise_kernel(const uint64_t* __restri
                                                         uint32_t logN, uint32_t L) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_pairs;
        i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t e = i << 1;
-    const uint32_t limb = (uint32_t)((e >> logN) % L);
-    const uint64_t q = qs[limb], mu = mus[limb];
-    const uint32_t s = bits[limb];
     const ulonglong2 va = reinterpret_cast<const ulonglong2*>(A)[i];
     const ulonglong2 vb = reinterpret_cast<const ulonglong2*>(B)[i];
+    const uint32_t limb = (uint32_t)(i >> (logN - 1)) % L;   // fewer than 2^31 vectors
+    const uint64_t q = qs[limb], mu = mus[limb];
+    const uint32_t s = bits[limb];
     ulonglong2 vc;
     vc.x = mulmod_barrett(va.x, vb.x, q, mu, s);
     vc.y = mulmod_barrett(va.y, vb.y, q, mu, s);

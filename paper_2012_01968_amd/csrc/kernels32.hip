@@ -569,7 +569,7 @@ __global__ __launch_bounds__(256) void pointwise32_kernel(const uint32_t* __rest
                                                           const uint64_t* __restrict__ mus, uint64_t n,
                                                           uint32_t logN, uint32_t L) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t limb = (uint32_t)((i >> logN) % L);
+    const uint32_t limb = (uint32_t)(i >> logN) % L;   // fewer than 2^31 vectors
     const uint32_t q = qs[limb];
     const uint64_t x = (uint64_t)A[i] * B[i];
     const uint64_t r = x - __umul64hi(x, mus[limb]) * q;

@@ -9,10 +9,11 @@
 // sums: at most 513 digit products of at most 2^14, below 2^24.  The tables come from
 // crt_math.hpp (host), laid out as the instruction's operands.
 //
-// A workgroup of four waves takes 256 coefficients, 64 per wave (two column groups of 32).  The
-// coefficients' digits stay in registers for the whole kernel, and the constant matrix streams
-// through LDS one 32-row tile at a time, loaded while the previous tile is multiplied, so each
-// workgroup reads the matrix (132 KB at 45 primes) once from L2.
+// A workgroup of four waves takes 128 coefficients, one column group of 32 per wave (two groups per
+// wave need 172 VGPRs, two waves per SIMD, at 45 primes: decomposition 42 us instead of 38).  The
+// coefficients' digits stay in registers for the whole kernel, their loads issued together, and the
+// constant matrix streams through LDS one 32-row tile at a time, loaded while the previous tile
+// is multiplied, so each workgroup reads the matrix (132 KB at 45 primes) once from L2.
 #include "kernels.hpp"
 #include "passes.hpp"
 
@@ -22,7 +23,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kCvtThreads = 256;
-constexpr int kCvtGroups = 2;                        // column groups of 32 coefficients per wave
+constexpr int kCvtGroups = 1;                        // column groups of 32 coefficients per wave
 constexpr int kCvtCoeffs = kCvtThreads / 64 * 32 * kCvtGroups;
 constexpr uint64_t kDigitBias = 0x8080808080808080ull;
 
@@ -106,11 +107,11 @@ __device__ __forceinline__ int64_t columns4(const v16i& c, int64_t add) {
 // The bytes enter as signed digits less 128, `offsets` adds the 128s back.  With s = bitlen(q_l),
 // t = floor(V / 2^(s-15)) < 2^32 and mu = floor(2^(s+31) / q_l) < 2^32, the estimate
 // floor(t mu / 2^46) of V / q_l falls short by less than 1 + 2^-13, so V - est q_l < 2 q_l.
-// 2 x 2^16 coefficients at 45 primes of 60 bits: 42 us (2.2 TB/s of words and residues; 132 matrix
+// 2 x 2^16 coefficients at 45 primes of 60 bits: 34 us (2.7 TB/s of words and residues; 132 matrix
 // instructions per 32 coefficients are 7 us of it), against 201 us for one exact Shoup product per
 // word and prime.  Bound by the loads of a wave's digits, which nothing of the same wave overlaps.
 template <int KS>
-__global__ __launch_bounds__(kCvtThreads, 2) void rns_decompose_kernel(
+__global__ __launch_bounds__(kCvtThreads) void rns_decompose_kernel(
     const uint64_t* __restrict__ words, uint32_t W, uint64_t* __restrict__ res, uint64_t n_coeffs, uint32_t logN,
     uint32_t L, const v4i* __restrict__ frag, uint32_t stride, const DecomposePrime* __restrict__ primes,
     const int64_t* __restrict__ offsets, uint32_t all_wide) {
@@ -130,9 +131,14 @@ __global__ __launch_bounds__(kCvtThreads, 2) void rns_decompose_kernel(
     for (int s = 0; s < KS; ++s) {
       const uint32_t w = 4 * s + 2 * h;
       const uint64_t a0 = w < W ? x[(size_t)w * N] : 0, a1 = w + 1 < W ? x[(size_t)(w + 1) * N] : 0;
-      b[g][s] = digits16(a0 ^ kDigitBias, a1 ^ kDigitBias);
+      b[g][s] = digits16(a0, a1);
     }
   }
+  loads_issued();
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) b[g][s] ^= (int)0x80808080;
   for_matrix_tiles<KS>(frag, stride, (L + 3) / 4, S, lds, [&](uint32_t t, const v4i* tile) {
     const uint32_t l0 = 4 * t + 2 * h;
     v16i acc[kCvtGroups];
@@ -166,15 +172,16 @@ __global__ __launch_bounds__(kCvtThreads, 2) void rns_decompose_kernel(
 // units gives k, or k + 1 when x lies within 2^-45 Q of Q; then x - Q < 0 shows in the sign of
 // the result and Q is added back.  Each lane half holds 16 consecutive base-256 columns of a
 // tile, carries them into four 32-bit words and passes its carry on (half 0 to half 1, half 1 to
-// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 39 us, against 576 us for
+// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 38 us, against 576 us for
 // 64-bit products with a carry chain per product (93.6 M products of 64 x 64 bits at one wave per
 // SIMD) and a search for k; the same 132 matrix instructions as the decomposition.
 template <int KS>
-__global__ __launch_bounds__(kCvtThreads, 2) void crt_reconstruct_kernel(
+__global__ __launch_bounds__(kCvtThreads) void crt_reconstruct_kernel(
     const uint64_t* __restrict__ res, uint64_t* __restrict__ out, uint64_t n_coeffs, uint32_t logN, uint32_t L,
     uint32_t W, const v4i* __restrict__ frag, const ReconstructPrime* __restrict__ primes,
     const uint64_t* __restrict__ Q) {
   __shared__ v4i lds[2][KS * 64];
+  __shared__ ReconstructPrime pl[4 * KS];   // the primes' constants: a wave meets them one by one
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = L / 4 + 1, T = W / 4 + 1;
   const uint64_t N = 1ull << logN;
   const uint64_t j0 = (uint64_t)blockIdx.x * kCvtCoeffs + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
@@ -190,6 +197,19 @@ __global__ __launch_bounds__(kCvtThreads, 2) void crt_reconstruct_kernel(
     o[g] = out + p * W * N + c;
     frac[g] = 0;
   }
+  uint64_t r[kCvtGroups][KS][2];
+#pragma unroll
+  for (int g = 0; g < kCvtGroups; ++g)
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t l = 4 * s + 2 * h + u;
+        r[g][s][u] = l < L ? in[g][(size_t)l * N] : 0;
+      }
+  loads_issued();
+  if (threadIdx.x < L) pl[threadIdx.x] = primes[threadIdx.x];
+  __syncthreads();
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     uint64_t y[kCvtGroups][2];
@@ -199,11 +219,11 @@ __global__ __launch_bounds__(kCvtThreads, 2) void crt_reconstruct_kernel(
 #pragma unroll
       for (int g = 0; g < kCvtGroups; ++g) y[g][u] = 0;
       if (l < L) {
-        const ReconstructPrime pr = primes[l];
+        const ReconstructPrime pr = pl[l];
         const uint32_t sh = __clzll(pr.q) - 2;
 #pragma unroll
         for (int g = 0; g < kCvtGroups; ++g) {
-          y[g][u] = csub(shoup_exact(in[g][(size_t)l * N], pr.inv, pr.inv_b, pr.q), pr.q);
+          y[g][u] = csub(shoup_exact(r[g][s][u], pr.inv, pr.inv_b, pr.q), pr.q);
           frac[g] += __umul64hi(y[g][u] << sh, pr.rec);
         }
       }

@@ -97,6 +97,13 @@ struct TablePack {
 
 }  // namespace
 
+// Persistent workgroups of a fused launch.  Resident workgroups whose vector is not through its first
+// pass wait, and their polling holds up the ones that work: forward + inverse at 256 / 512 / 1024
+// workgroups (1, 2, 4 per CU) takes 74 / 98 / 119 us at 2^14 x 90 vectors, 62 / 93 / 111 at 2^15 x 40,
+// 180 / 166 / 219 at 2^16 x 90 and 127 / 127 / 218 at 2^17 x 20 (two rebuilt stages: 72 / 93 / 114,
+// 62 / 95 / 115, 181 / 159 / 202, 125 / 124 / 141).
+static uint32_t fused_grid_for(uint32_t logN) { return logN <= 15 ? 256 : 512; }
+
 struct ntt_plan_s {
   uint32_t N = 0, logN = 0, L = 0, logN1 = 0;
   int32_t twiddle_mode = NTT_TWIDDLE_TABLE;
@@ -110,7 +117,7 @@ struct ntt_plan_s {
   bool auto_split = false;                // the split and the tile shape are the library's choice
   uint32_t debug = 0;                     // split-pass debug modes (NTT_DEBUG at creation)
   uint32_t fused_lag = 4;                 // vectors an XCD queue runs pass 1 ahead of pass 2
-  uint32_t fused_grid = 1024;             // persistent workgroups (4 per CU)
+  uint32_t fused_grid = 512;              // persistent workgroups (fused_grid_for)
   uint32_t* d_ctr = nullptr;              // fused-launch counters: 16 + kMaxFusedVectors words
   std::mutex fused_mu;                    // orders fused launches of this plan across streams
   hipEvent_t fused_ev = nullptr;
@@ -435,6 +442,7 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
     // through the Infinity Cache, and the fused queue measured slower (see the design notes).
     p->kernel_path = (stage_path || w32) ? (w32 ? NTT_PATH_SPLIT : o.kernel_path)
                                 : (o.kernel_path == NTT_PATH_FUSED && can_fuse) ? NTT_PATH_FUSED : NTT_PATH_SPLIT;
+    p->fused_grid = fused_grid_for(p->logN);
     if (const char* e = std::getenv("NTT_FUSED_LAG")) p->fused_lag = (uint32_t)std::max(1, std::atoi(e));
     if (const char* e = std::getenv("NTT_FUSED_GRID")) p->fused_grid = (uint32_t)std::max(1, std::atoi(e));
   }

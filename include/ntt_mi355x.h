@@ -58,7 +58,7 @@ typedef enum {
     NTT_ERR_UNSUPPORTED = -6   /* option combination not built into the library    */
 } ntt_status;
 
-/* Twiddle sources (Section VII).  TABLE reads every twiddle and its Shoup companion
+/* Twiddle sources (Section VII).  TABLE reads every twiddle and its companion
  * from a precomputed table; OT ("on-the-fly twiddling") rebuilds the twiddles of the
  * last `ot_stages` forward stages (first inverse stages) from two small base tables by
  * multiplying the operand by both factors in turn. */

@@ -125,7 +125,7 @@ struct ntt_plan_s {
   bool fused_pending = false;
   int device = 0;
   bool tuned = false; // options taken from the tuner's file (use_autotune)
-  bool fast = false;  // all primes below 2^60 (wider lazy ranges, estimated quotients)
+  bool fast = false;  // all primes below 2^60 (signed Montgomery products)
   std::vector<uint64_t> primes, psis;
 
   void* d_small = nullptr;    // the small tables' memory: d_q, d_mc, OT tables, d_scale*, d_mu, d_bits, *32

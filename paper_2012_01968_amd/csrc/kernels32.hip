@@ -11,10 +11,10 @@
 // sums (Gentleman-Sande) are brought back into [-q, q) when a stage's outputs would pass 2 q.
 //
 // Measured at N = 2^16, 90 primes, 2 polynomials, forward + inverse: 129 us before (one column per lane,
-// tables of two words, vectorised neither way, rows not grouped by prime), 98 us now: column passes
-// 20-22 us (94 MB), row passes 32 us (118 MB, of them 24 MB of twiddles where 47 MB were).  Between
+// tables of two words, vectorised neither way, rows not grouped by prime), 95 us now: column passes
+// 20-21 us (94 MB), row passes 31 us (118 MB, of them 24 MB of twiddles where 47 MB were).  Between
 // the byte and the instruction bound (16 us): 1.4 rounds of the chip's wave slots leave little
-// overlap between waves.  Product at N = 2^14, 20 primes, 2 polynomials: 44 -> 21 us.
+// overlap between waves.  Product at N = 2^14, 20 primes, 2 polynomials: 44 -> 20 us.
 //
 // Same two-pass structure as the 64-bit kernels (Section VI-C): a column pass over the first
 // log2 N1 stages and a row pass over the rest, registers between LDS exchanges; N <= 2^12 runs in

@@ -1,4 +1,4 @@
-// Forward NTT kernels, primes below 2^60 (estimated quotients).
+// Forward NTT kernels, primes below 2^60 (signed Montgomery products).
 #include "kernels_impl.hpp"
 
 namespace nttk {

@@ -645,7 +645,6 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void inv_col_kernel(PassA
 constexpr int row_t(int logm, int lr) { return (1 << logm) >> (lr < logm ? lr : logm); }
 constexpr int row_nth_canon(int logm, int lr, int nth) { return row_t(logm, lr) >= nth ? row_t(logm, lr) : nth; }
 
-//
 // Default shape: 8 values per lane and 128 lanes; 4 values and 64 lanes for row passes of at most
 // kSmallRows residues, whose 8-value waves would not fill the SIMDs four deep, so that a wave's own
 // chain of stages is what the launch waits for.  Forward + inverse, us, 8 x 128 / 4 x 64: N = 2^13 x 7

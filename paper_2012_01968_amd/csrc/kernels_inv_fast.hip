@@ -1,4 +1,4 @@
-// Inverse NTT kernels, primes below 2^60 (estimated quotients).
+// Inverse NTT kernels, primes below 2^60 (signed Montgomery products).
 #include "kernels_impl.hpp"
 
 namespace nttk {

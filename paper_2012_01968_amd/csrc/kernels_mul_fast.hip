@@ -1,4 +1,4 @@
-// Row passes with a key product, primes below 2^60 (estimated quotients).
+// Row passes with a key product, primes below 2^60 (signed Montgomery products).
 #include "kernels_impl.hpp"
 
 namespace nttk {

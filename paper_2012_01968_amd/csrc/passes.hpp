@@ -129,7 +129,7 @@ struct Steps {
 };
 
 // On-the-fly twiddling (Section VII): Psi[ix] = psi^{e}, e = brv_logN(ix), is split into
-// base-B digits e = e_lo + B * e_hi and applied as two Shoup products with the stored
+// base-B digits e = e_lo + B * e_hi and applied as two products with the stored
 // factors psi^{e_lo} and psi^{B * e_hi}.
 struct OtTables {
   const Tw* lo;

@@ -1,5 +1,5 @@
 // Host-side number theory for building a plan: primality, the root convention and the
-// twiddle tables with their Shoup companions.  Written independently of any test code.
+// twiddle tables with their companions.  Written independently of any test code.
 #pragma once
 #include <stdint.h>
 #include <vector>

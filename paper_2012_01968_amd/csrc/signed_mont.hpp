@@ -19,8 +19,8 @@
 // fifth stage (it was every other stage with unsigned values below 16 q).
 //
 // Measured on the kernels (VALU instructions of a wave, before and after): 256-point forward row
-// 1019 and 764, 512-point two-operand product row 3057 and 2404; product of 2 polynomials at
-// N = 2^17, 60 primes 362 and 308 us, forward and inverse of 2 polynomials at N = 2^16, 45 primes
+// 1019 and 764, 512-point two-operand product row 3057 and 2404 (740 and 2117 since the rows are one
+// basic block); product of 2 polynomials at N = 2^17, 60 primes 362 and 308 us (301 with that), forward and inverse of 2 polynomials at N = 2^16, 45 primes
 // with the tables cached 103 and 91 us.
 #pragma once
 #include <stdint.h>

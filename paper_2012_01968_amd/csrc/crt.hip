@@ -9,7 +9,7 @@
 // sums: at most 513 digit products of at most 2^14, below 2^24.  The tables come from
 // crt_math.hpp (host), laid out as the instruction's operands.
 //
-// A workgroup of four waves takes 128 coefficients, one column group of 32 per wave (two groups per
+// A workgroup of four or eight waves takes 128 or 256 coefficients, one column group of 32 per wave (two groups per
 // wave need 172 VGPRs, two waves per SIMD, at 45 primes: decomposition 42 us instead of 38).  The
 // coefficients' digits stay in registers for the whole kernel, their loads issued together, and the
 // constant matrix streams through LDS one 32-row tile at a time, loaded while the previous tile
@@ -22,9 +22,8 @@ namespace nttk {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kCvtThreads = 256;
 constexpr int kCvtGroups = 1;                        // column groups of 32 coefficients per wave
-constexpr int kCvtCoeffs = kCvtThreads / 64 * 32 * kCvtGroups;
+constexpr int cvt_coeffs(int nth) { return nth / 64 * 32 * kCvtGroups; }
 constexpr uint64_t kDigitBias = 0x8080808080808080ull;
 
 // b * w mod q in [0, 2q) for any b < 2^64, q < 2^62 (Shoup with the exact quotient).
@@ -47,23 +46,23 @@ __device__ __forceinline__ Halves halves(uint32_t x) {
 
 // Streams the matrix tiles [T][S][64 lanes][16 digits] through two LDS buffers: `body(t, lds)` runs
 // with tile t's S slices in `lds`.  Every wave of the workgroup takes part in every tile.
-template <int KS, typename F>
+template <int KS, int NTH, typename F>
 __device__ __forceinline__ void for_matrix_tiles(const v4i* __restrict__ frag, uint32_t stride, uint32_t T, uint32_t S,
                                                  v4i (&lds)[2][KS * 64], F&& body) {
-  constexpr int PER = (KS * 64 + kCvtThreads - 1) / kCvtThreads;
+  constexpr int PER = (KS * 64 + NTH - 1) / NTH;
   const uint32_t tid = threadIdx.x, n = S * 64;
   v4i next[PER];
   auto fetch = [&](uint32_t t) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const uint32_t e = tid + i * kCvtThreads;
+      const uint32_t e = tid + i * NTH;
       if (e < n) next[i] = frag[(size_t)t * stride * 64 + e];
     }
   };
   auto put = [&](v4i* dst) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const uint32_t e = tid + i * kCvtThreads;
+      const uint32_t e = tid + i * NTH;
       if (e < n) dst[e] = next[i];
     }
   };
@@ -107,18 +106,18 @@ __device__ __forceinline__ int64_t columns4(const v16i& c, int64_t add) {
 // The bytes enter as signed digits less 128, `offsets` adds the 128s back.  With s = bitlen(q_l),
 // t = floor(V / 2^(s-15)) < 2^32 and mu = floor(2^(s+31) / q_l) < 2^32, the estimate
 // floor(t mu / 2^46) of V / q_l falls short by less than 1 + 2^-13, so V - est q_l < 2 q_l.
-// 2 x 2^16 coefficients at 45 primes of 60 bits: 34 us (2.7 TB/s of words and residues; 132 matrix
+// 2 x 2^16 coefficients at 45 primes of 60 bits: 32 us (2.8 TB/s of words and residues; 132 matrix
 // instructions per 32 coefficients are 7 us of it), against 201 us for one exact Shoup product per
 // word and prime.  Bound by the loads of a wave's digits, which nothing of the same wave overlaps.
-template <int KS>
-__global__ __launch_bounds__(kCvtThreads) void rns_decompose_kernel(
+template <int KS, int NTH>
+__global__ __launch_bounds__(NTH) void rns_decompose_kernel(
     const uint64_t* __restrict__ words, uint32_t W, uint64_t* __restrict__ res, uint64_t n_coeffs, uint32_t logN,
     uint32_t L, const v4i* __restrict__ frag, uint32_t stride, const DecomposePrime* __restrict__ primes,
     const int64_t* __restrict__ offsets, uint32_t all_wide) {
   __shared__ v4i lds[2][KS * 64];
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = (W + 3) / 4;
   const uint64_t N = 1ull << logN;
-  const uint64_t j0 = (uint64_t)blockIdx.x * kCvtCoeffs + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
+  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
   v4i b[kCvtGroups][KS];
   uint64_t* out[kCvtGroups];
 #pragma unroll
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(kCvtThreads) void rns_decompose_kernel(
   for (int g = 0; g < kCvtGroups; ++g)
 #pragma unroll
     for (int s = 0; s < KS; ++s) b[g][s] ^= (int)0x80808080;
-  for_matrix_tiles<KS>(frag, stride, (L + 3) / 4, S, lds, [&](uint32_t t, const v4i* tile) {
+  for_matrix_tiles<KS, NTH>(frag, stride, (L + 3) / 4, S, lds, [&](uint32_t t, const v4i* tile) {
     const uint32_t l0 = 4 * t + 2 * h;
     v16i acc[kCvtGroups];
     tile_product<KS>(acc, tile, b, S, lane);
@@ -172,11 +171,11 @@ __global__ __launch_bounds__(kCvtThreads) void rns_decompose_kernel(
 // units gives k, or k + 1 when x lies within 2^-45 Q of Q; then x - Q < 0 shows in the sign of
 // the result and Q is added back.  Each lane half holds 16 consecutive base-256 columns of a
 // tile, carries them into four 32-bit words and passes its carry on (half 0 to half 1, half 1 to
-// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 38 us, against 576 us for
+// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 37 us, against 576 us for
 // 64-bit products with a carry chain per product (93.6 M products of 64 x 64 bits at one wave per
 // SIMD) and a search for k; the same 132 matrix instructions as the decomposition.
-template <int KS>
-__global__ __launch_bounds__(kCvtThreads) void crt_reconstruct_kernel(
+template <int KS, int NTH>
+__global__ __launch_bounds__(NTH) void crt_reconstruct_kernel(
     const uint64_t* __restrict__ res, uint64_t* __restrict__ out, uint64_t n_coeffs, uint32_t logN, uint32_t L,
     uint32_t W, const v4i* __restrict__ frag, const ReconstructPrime* __restrict__ primes,
     const uint64_t* __restrict__ Q) {
@@ -184,7 +183,7 @@ __global__ __launch_bounds__(kCvtThreads) void crt_reconstruct_kernel(
   __shared__ ReconstructPrime pl[4 * KS];   // the primes' constants: a wave meets them one by one
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = L / 4 + 1, T = W / 4 + 1;
   const uint64_t N = 1ull << logN;
-  const uint64_t j0 = (uint64_t)blockIdx.x * kCvtCoeffs + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
+  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
   v4i b[kCvtGroups][KS];
   uint64_t* o[kCvtGroups];
   const uint64_t* in[kCvtGroups];
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(kCvtThreads) void crt_reconstruct_kernel(
   }
   uint32_t carry[kCvtGroups] = {};   // out of the previous tile (signed)
   uint32_t negative[kCvtGroups] = {};
-  for_matrix_tiles<KS>(frag, S, T, S, lds, [&](uint32_t t, const v4i* tile) {
+  for_matrix_tiles<KS, NTH>(frag, S, T, S, lds, [&](uint32_t t, const v4i* tile) {
     v16i acc[kCvtGroups];
     tile_product<KS>(acc, tile, b, S, lane);
 #pragma unroll
@@ -291,7 +290,19 @@ __global__ __launch_bounds__(kCvtThreads) void crt_reconstruct_kernel(
 // each), so a short chain does not pay for a long one's registers.
 #define NTTK_CVT_CASES(X) X(2) X(4) X(8) X(12) X(17)
 
-static uint32_t cvt_blocks(uint64_t n) { return (uint32_t)((n + kCvtCoeffs - 1) / kCvtCoeffs); }
+// f(lanes of a workgroup) for a launch over n coefficients: 512 where that still gives every CU one,
+// since each workgroup reads the whole matrix.  256 / 512 lanes, us: 2^16 coefficients at 45 primes
+// decomposition 25.0 / 24.0, reconstruction 26.9 / 25.3; 2^17 33.3 / 32.2 and 39.0 / 36.6; 2^18 at 30
+// primes 48.6 / 47.9 and 50.5 / 47.9; but 2^15 at 24 primes (128 workgroups) 9.7 / 9.5 and
+// 10.3 / 11.0.
+constexpr uint64_t kWideCvt = 1u << 16;
+template <typename F>
+static hipError_t with_cvt_threads(uint64_t n, F&& f) {
+  return n >= kWideCvt ? f(std::integral_constant<int, 512>{}) : f(std::integral_constant<int, 256>{});
+}
+static uint32_t cvt_blocks(uint64_t n, int nth) {
+  return (uint32_t)((n + cvt_coeffs(nth) - 1) / cvt_coeffs(nth));
+}
 
 hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res, uint32_t n_polys, uint32_t logN,
                                 uint32_t L, const void* frag, uint32_t frag_slices, const DecomposePrime* primes,
@@ -299,16 +310,19 @@ hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res
   const uint64_t n = (uint64_t)n_polys << logN;
   const uint32_t S = (W + 3) / 4;
   if (W == 0 || S > frag_slices) return hipErrorInvalidValue;
+  return with_cvt_threads(n, [&](auto nth) {
+    constexpr int NTH = decltype(nth)::value;
 #define X(KS)                                                                                                      \
-  if (S <= KS) {                                                                                                   \
-    hipLaunchKernelGGL(rns_decompose_kernel<KS>, dim3(cvt_blocks(n)), dim3(kCvtThreads), 0, st, words, W, res, n,  \
-                       logN, L, static_cast<const v4i*>(frag), frag_slices, primes, offsets + (size_t)S * L * 2,   \
-                       (uint32_t)all_wide);                                                                        \
-    return hipGetLastError();                                                                                      \
-  }
-  NTTK_CVT_CASES(X)
+    if (S <= KS) {                                                                                                 \
+      hipLaunchKernelGGL((rns_decompose_kernel<KS, NTH>), dim3(cvt_blocks(n, NTH)), dim3(NTH), 0, st, words, W,    \
+                         res, n, logN, L, static_cast<const v4i*>(frag), frag_slices, primes,                      \
+                         offsets + (size_t)S * L * 2, (uint32_t)all_wide);                                         \
+      return hipGetLastError();                                                                                    \
+    }
+    NTTK_CVT_CASES(X)
 #undef X
-  return hipErrorInvalidValue;
+    return hipErrorInvalidValue;
+  });
 }
 
 hipError_t launch_crt_reconstruct(const uint64_t* res, uint64_t* out, uint32_t n_polys, uint32_t logN, uint32_t L,
@@ -317,15 +331,18 @@ hipError_t launch_crt_reconstruct(const uint64_t* res, uint64_t* out, uint32_t n
   const uint64_t n = (uint64_t)n_polys << logN;
   const uint32_t S = L / 4 + 1;
   if (L > 64) return hipErrorInvalidValue;   // k must fit one digit
-#define X(KS)                                                                                                       \
-  if (S <= KS) {                                                                                                    \
-    hipLaunchKernelGGL(crt_reconstruct_kernel<KS>, dim3(cvt_blocks(n)), dim3(kCvtThreads), 0, st, res, out, n, logN, \
-                       L, W, static_cast<const v4i*>(frag), primes, Q);                                             \
-    return hipGetLastError();                                                                                       \
-  }
-  NTTK_CVT_CASES(X)
+  return with_cvt_threads(n, [&](auto nth) {
+    constexpr int NTH = decltype(nth)::value;
+#define X(KS)                                                                                                      \
+    if (S <= KS) {                                                                                                 \
+      hipLaunchKernelGGL((crt_reconstruct_kernel<KS, NTH>), dim3(cvt_blocks(n, NTH)), dim3(NTH), 0, st, res, out,  \
+                         n, logN, L, W, static_cast<const v4i*>(frag), primes, Q);                                 \
+      return hipGetLastError();                                                                                    \
+    }
+    NTTK_CVT_CASES(X)
 #undef X
-  return hipErrorInvalidValue;
+    return hipErrorInvalidValue;
+  });
 }
 
 }  // namespace nttk

@@ -52,3 +52,28 @@ def test_conversion_tile_edges(L, bits, logN, P):
             assert np.array_equal(host(res), oracle.rns_decompose_words(wide, primes)), f"decompose {Wx} words"
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("L,bits", [(5, 60), (13, 60), (29, 61), (45, 60), (64, 62)])   # one per kernel
+def test_conversion_wide_workgroups(L, bits):
+    """Launches of 2^16 coefficients and more, whose workgroups have 512 lanes: 513 polynomials of 128
+    coefficients end half way through one.  Against the oracle; exact."""
+    N, P = 128, 513
+    primes = synth.gen_primes(9900 + L, N, bits, L)
+    Q = 1
+    for q in primes:
+        Q *= q
+    plan = ntt.ntt_plan_create(N, primes)
+    try:
+        W = ntt.ntt_crt_words(plan)
+        words = np.stack([synth.uniform_wide(9950 + L, p, Q, N) for p in range(P)])
+        edge = [0, Q - 1, 1, Q - 2]
+        words[P - 1, :, N - len(edge):] = synth.ints_to_words(edge, W)
+        res = torch.empty((P, L, N), dtype=torch.int64, device="cuda")
+        ntt.ntt_rns_decompose(plan, dev(words), W, res)
+        assert np.array_equal(host(res), oracle.rns_decompose_words(words, primes)), "decompose"
+        out = torch.full((P, W, N), -1, dtype=torch.int64, device="cuda")
+        ntt.ntt_crt_reconstruct(plan, res, out)
+        assert np.array_equal(host(out), words), "reconstruct"
+    finally:
+        plan.destroy()

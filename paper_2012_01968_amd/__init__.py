@@ -242,6 +242,17 @@ def _first_current_stream() -> int:
 _current_stream = _first_current_stream
 
 
+def _ask_torch_again() -> None:
+    global _current_stream
+    _current_stream = _first_current_stream
+
+
+# A forked child of a process that has used the GPU cannot use it, and torch's own query says so; the
+# raw ones below it do not look.
+if hasattr(os, "register_at_fork"):
+    os.register_at_fork(after_in_child=_ask_torch_again)
+
+
 def _stream(stream) -> int | None:
     if stream is None:
         return _current_stream() or None

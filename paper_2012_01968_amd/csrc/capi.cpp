@@ -1052,6 +1052,21 @@ namespace nttk {
 hipError_t launch_copy16(const void* src, void* dst, uint64_t n16, hipStream_t st);
 }  // namespace nttk
 
+// f(first polynomial, polynomials) over a conversion's launches: their kernels take two lanes per
+// coefficient and a launch has fewer than 2^32 lanes, so 2^30 coefficients at most go at once.
+static constexpr uint64_t kConvertCoeffs = 1u << 30;
+template <typename F>
+static hipError_t for_conversion_launches(ntt_plan_t plan, uint32_t n_polys, F&& f) {
+  const uint32_t step = (uint32_t)(kConvertCoeffs >> plan->logN);
+  for (uint32_t p = 0; p < n_polys;) {
+    const uint32_t n = std::min(step, n_polys - p);
+    const hipError_t e = f((size_t)p, n);
+    if (e != hipSuccess) return e;
+    p += n;
+  }
+  return hipSuccess;
+}
+
 extern "C" {
 
 ntt_status ntt_plan_create(ntt_plan_t* out, uint32_t N, const uint64_t* primes, uint32_t L,
@@ -1653,10 +1668,12 @@ ntt_status ntt_rns_decompose(ntt_plan_t plan, const uint64_t* d_words, uint32_t 
     if ((s = crt_prepare(plan))) return s;
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
-    const hipError_t e = nttk::launch_rns_decompose(d_words, n_words, d_res, n_polys, plan->logN, plan->L,
-                                                    plan->crt.dec, nttc::kDecomposeSlices, plan->crt.dec_primes,
-                                                    plan->crt.dec_off, plan->crt.all_wide,
-                                                    static_cast<hipStream_t>(stream));
+    const hipError_t e = for_conversion_launches(plan, n_polys, [&](size_t p, uint32_t n) {
+      return nttk::launch_rns_decompose(d_words + p * n_words * plan->N, n_words, d_res + p * plan->L * plan->N, n,
+                                        plan->logN, plan->L, plan->crt.dec, nttc::kDecomposeSlices,
+                                        plan->crt.dec_primes, plan->crt.dec_off, plan->crt.all_wide,
+                                        static_cast<hipStream_t>(stream));
+    });
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_rns_decompose launch");
   } catch (const std::bad_alloc&) {
     return fail(NTT_ERR_NOMEM, "host allocation failed");
@@ -1676,9 +1693,11 @@ ntt_status ntt_crt_reconstruct(ntt_plan_t plan, const uint64_t* d_res, uint64_t*
     if ((s = crt_prepare(plan))) return s;
     DeviceGuard g(plan->device);
     if (!g.ok) return fail(NTT_ERR_HIP, "cannot select the plan's device");
-    const hipError_t e = nttk::launch_crt_reconstruct(d_res, d_words, n_polys, plan->logN, plan->L, plan->crt.W,
-                                                      plan->crt.rec, plan->crt.rec_primes, plan->crt.Q,
-                                                      static_cast<hipStream_t>(stream));
+    const hipError_t e = for_conversion_launches(plan, n_polys, [&](size_t p, uint32_t n) {
+      return nttk::launch_crt_reconstruct(d_res + p * plan->L * plan->N, d_words + p * plan->crt.W * plan->N, n,
+                                          plan->logN, plan->L, plan->crt.W, plan->crt.rec, plan->crt.rec_primes,
+                                          plan->crt.Q, static_cast<hipStream_t>(stream));
+    });
     return e == hipSuccess ? NTT_OK : hip_fail(e, "ntt_crt_reconstruct launch");
   } catch (const std::bad_alloc&) {
     return fail(NTT_ERR_NOMEM, "host allocation failed");

@@ -41,7 +41,8 @@ FLAGS = [
 
 # Host-only sources: they decide which launches happen but hold no device code, so a change
 # there leaves every kernel's measured time (and the counters taken of it) valid.
-HOST_ONLY_SOURCES = ("capi.cpp", "plan_math.hpp", "plan_life.hpp", "tune_file.hpp", "crt_math.hpp")
+HOST_ONLY_SOURCES = ("capi.cpp", "plan_math.hpp", "plan_life.hpp", "tune_file.hpp", "crt_math.hpp",
+                     "launch_rules.hpp")
 # Device code that no plan launches (the calibration copy): outside the hash as well.
 UNHASHED_DEVICE_SOURCES = ("calib.hip",)
 

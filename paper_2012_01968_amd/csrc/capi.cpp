@@ -19,6 +19,7 @@
 
 #include "crt_math.hpp"
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 #include "passes.hpp"
 #include "plan_life.hpp"
 #include "plan_math.hpp"
@@ -239,20 +240,8 @@ struct ntt_plan_s {
   nttk::Plan32 plan32() const {
     return nttk::Plan32{d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul, d_primes32, L, logN, logN1};
   }
-  // log2 N1 of a launch over n_vec vectors of an automatic plan (the tables serve every split):
-  //  * N = 2^13 takes one pass (1024 lanes and 68 KB of LDS per vector) where the vectors fill the
-  //    chip: forward + inverse of 240 vectors 28 us against 33 us, products 31 against 41; 7 vectors
-  //    22.6 against 13.1.  (Between them, 120 vectors take the same time either way.)
-  //  * N = 2^15 and 2^16 take columns of 2^7 points up to 2^21 residues, where the shorter rows' chain
-  //    of stages counts: 39 vectors of 2^15 28.6 us against 29.3 (62-bit primes 33.4 against 35.2), 21 of
-  //    2^16 32.2 against 33.7 (37.5 against 39.7); above, 90 vectors of 2^15 52.5 against 50.5 with 2^6.
-  static constexpr uint64_t kOnePassVectors = 192;
-  static constexpr uint64_t kSmallLaunch = 1u << 21;
-  uint32_t split_for(uint64_t n_vec) const {
-    if (auto_split && logN == 13 && n_vec >= kOnePassVectors) return 0;
-    if (auto_split && (logN == 15 || logN == 16) && (n_vec << logN) <= kSmallLaunch) return 7;
-    return logN1;
-  }
+  // log2 N1 of a launch over n_vec vectors (launch_rules.hpp)
+  uint32_t split_for(uint64_t n_vec) const { return auto_split ? nttr::split(logN, logN1, n_vec, fast) : logN1; }
   int active_ot() const { return twiddle_mode == NTT_TWIDDLE_OT ? ot_stages : 0; }
   // the paths whose data goes back to global memory after every group of stages
   bool stage_path() const { return kernel_path == NTT_PATH_RADIX2 || kernel_path == NTT_PATH_REGISTER; }

@@ -1610,7 +1610,7 @@ static ntt_status crt_prepare(ntt_plan_t plan) {
     const uint64_t q = plan->primes[l];
     int s = 0;
     while (s < 64 && (q >> s)) ++s;
-    dp[l] = {q, (uint32_t)(((nttp::u128)1 << (s + 31)) / q), s - 15};
+    dp[l] = {q, (uint32_t)(((nttp::u128)1 << (s + 31)) / q), s - 15, (uint64_t)(((nttp::u128)1 << 64) / q)};
     rp[l] = {q, t.inv[l], nttp::shoup_companion(t.inv[l], q),
              (uint64_t)(((nttp::u128)1 << 120) / ((nttp::u128)q << (62 - s)))};
     all_wide = all_wide && s >= 47;

@@ -102,6 +102,20 @@ __device__ __forceinline__ int64_t columns4(const v16i& c, int64_t add) {
          (int64_t)c[R + 3] * (1 << 24);
 }
 
+// Integers of one word: a lane per residue and one exact product by floor(2^64 / q), which falls short of
+// x / q by less than 2.  Bound by its bytes; the digit matrices take a whole K slice for the word and
+// a fixed chain per tile (2^14 coefficients at 45 primes 3.7 us here, 12.0 there; 2^17 at 60 17.8 and 20.4).
+__global__ __launch_bounds__(256) void rns_decompose_word_kernel(const uint64_t* __restrict__ words,
+                                                                 uint64_t* __restrict__ res, uint64_t n_coeffs,
+                                                                 uint32_t logN, uint32_t L,
+                                                                 const DecomposePrime* __restrict__ primes) {
+  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint32_t l = blockIdx.y;
+  if (j >= n_coeffs) return;
+  const uint64_t q = primes[l].q, x = words[j];
+  res[((((j >> logN) * L + l) << logN) | (j & ((1ull << logN) - 1)))] = csub(x - __umul64hi(x, primes[l].recip) * q, q);
+}
+
 // Residue l of an integer x: V = sum_j byte_j (256^j mod q_l), below 2^17 q_l, then one reduction.
 // The bytes enter as signed digits less 128, `offsets` adds the 128s back.  With s = bitlen(q_l),
 // t = floor(V / 2^(s-15)) < 2^32 and mu = floor(2^(s+31) / q_l) < 2^32, the estimate
@@ -113,7 +127,7 @@ template <int KS, int NTH>
 __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
     const uint64_t* __restrict__ words, uint32_t W, uint64_t* __restrict__ res, uint64_t n_coeffs, uint32_t logN,
     uint32_t L, const v4i* __restrict__ frag, uint32_t stride, const DecomposePrime* __restrict__ primes,
-    const int64_t* __restrict__ offsets, uint32_t all_wide) {
+    const int64_t* __restrict__ offsets, uint32_t all_wide, uint32_t tiles_per) {
   __shared__ v4i lds[2][KS * 64];
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = (W + 3) / 4;
   const uint64_t N = 1ull << logN;
@@ -138,8 +152,10 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
   for (int g = 0; g < kCvtGroups; ++g)
 #pragma unroll
     for (int s = 0; s < KS; ++s) b[g][s] ^= (int)0x80808080;
-  for_matrix_tiles<KS, NTH>(frag, stride, (L + 3) / 4, S, lds, [&](uint32_t t, const v4i* tile) {
-    const uint32_t l0 = 4 * t + 2 * h;
+  const uint32_t t0 = blockIdx.y * tiles_per, left = (L + 3) / 4 - t0;   // this workgroup's tiles (decompose_parts)
+  for_matrix_tiles<KS, NTH>(frag + (size_t)t0 * stride * 64, stride, left < tiles_per ? left : tiles_per, S, lds,
+                            [&](uint32_t t, const v4i* tile) {
+    const uint32_t l0 = 4 * (t0 + t) + 2 * h;
     v16i acc[kCvtGroups];
     tile_product<KS>(acc, tile, b, S, lane);
     static_for<0, 2>([&](auto uc) {
@@ -304,19 +320,37 @@ static uint32_t cvt_blocks(uint64_t n, int nth) {
   return (uint32_t)((n + cvt_coeffs(nth) - 1) / cvt_coeffs(nth));
 }
 
+// Workgroups over the tiles of one decomposition launch of `blocks` workgroups over the coefficients: a
+// wave takes its tiles one after the other, so a small launch waits for that chain, and parts of it in
+// workgroups of their own cost only the digits read again.  Every part reads all digits, so wide
+// integers (more than 3 slices, 12 words) take fewer.  us, one part and the parts taken here: 2^12
+// coefficients of 42 words at 45 primes 17.6 / 5.5, of 4 words at 60 14.4 / 4.1; 2^14 of 56 words at 60 25.8 /
+// 11.3, of 12 words 16.7 / 5.9; 2^16 of 42 words at 45 21.2 / 18.0, of 4 words 12.7 / 9.3; 2^17 of 42 words (one
+// part) 31.6 against 37.2 with two.
+static uint32_t decompose_parts(uint32_t blocks, uint32_t tiles, uint32_t slices) {
+  const uint32_t parts = (slices <= 3 ? 1024u : 512u) / blocks;
+  return parts < 1 ? 1 : parts < tiles ? parts : tiles;
+}
+
 hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res, uint32_t n_polys, uint32_t logN,
                                 uint32_t L, const void* frag, uint32_t frag_slices, const DecomposePrime* primes,
                                 const int64_t* offsets, bool all_wide, hipStream_t st) {
   const uint64_t n = (uint64_t)n_polys << logN;
-  const uint32_t S = (W + 3) / 4;
+  const uint32_t S = (W + 3) / 4, T = (L + 3) / 4;
   if (W == 0 || S > frag_slices) return hipErrorInvalidValue;
+  if (W == 1 && L <= 65535) {   // primes along the grid's second dimension
+    hipLaunchKernelGGL(rns_decompose_word_kernel, dim3((uint32_t)((n + 255) / 256), L), dim3(256), 0, st, words, res, n,
+                       logN, L, primes);
+    return hipGetLastError();
+  }
   return with_cvt_threads(n, [&](auto nth) {
     constexpr int NTH = decltype(nth)::value;
+    const uint32_t blocks = cvt_blocks(n, NTH), parts = decompose_parts(blocks, T, S), per = (T + parts - 1) / parts;
 #define X(KS)                                                                                                      \
     if (S <= KS) {                                                                                                 \
-      hipLaunchKernelGGL((rns_decompose_kernel<KS, NTH>), dim3(cvt_blocks(n, NTH)), dim3(NTH), 0, st, words, W,    \
-                         res, n, logN, L, static_cast<const v4i*>(frag), frag_slices, primes,                      \
-                         offsets + (size_t)S * L * 2, (uint32_t)all_wide);                                         \
+      hipLaunchKernelGGL((rns_decompose_kernel<KS, NTH>), dim3(blocks, (T + per - 1) / per), dim3(NTH), 0, st,     \
+                         words, W, res, n, logN, L, static_cast<const v4i*>(frag), frag_slices, primes,            \
+                         offsets + (size_t)S * L * 2, (uint32_t)all_wide, per);                                    \
       return hipGetLastError();                                                                                    \
     }
     NTTK_CVT_CASES(X)

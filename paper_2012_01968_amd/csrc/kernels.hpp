@@ -68,6 +68,7 @@ struct DecomposePrime {
   uint64_t q;
   uint32_t mu;      // floor(2^(s+31) / q), s = bitlen(q)
   int32_t shift;    // s - 15
+  uint64_t recip;   // floor(2^64 / q)
 };
 struct ReconstructPrime {
   uint64_t q, inv, inv_b;   // (Q/q)^-1 mod q and its Shoup companion

@@ -21,6 +21,11 @@ namespace nttk {
 
 constexpr int kStageThreads = 256;
 
+template <int R>
+struct StageTw {   // the twiddles of a group, in the slots of StepSlots
+  Tw w[R], w2[R];
+};
+
 // Group of K stages starting at global stage s0 (forward) on every vector.  FINAL: this group
 // ends the transform (reduce to [0, q)).  Inverse (INV): stages run in Gentleman-Sande order;
 // CANON_IN: the group sees the caller's canonical input; SCALE0: the group holds global
@@ -47,7 +52,21 @@ __global__ __launch_bounds__(kStageThreads) void stage_group_kernel(PassArgs a, 
 #pragma unroll
   for (int u = 0; u < R; ++u) x[u] = p[(size_t)u << lo];
   if constexpr (!INV) {
-    ct_step<FAST, K, K, 0, 0, kCtLazy>(x, 0u, base, tabfn, ot, md);
+    if constexpr (FAST && K == 4) {
+      // All 15 twiddles go out with the data, in the order of their stages.  Left to the scheduler they sink
+      // to their uses, 19 waits for one load each: 24 x 2 vectors of 2^16 74.7 us that way and 62.1 this way, 6 of
+      // 2^14 21.3 and 16.0.  (The other radices lose nothing: 8 values 12.2 us at 24 x 2 of 2^11, 12.8 with it.)
+      StageTw<R> pre;
+      static_for_down<K, 0>([&](auto bit_c) {
+        constexpr int i = decltype(bit_c)::value, s = K - 1 - i;
+#pragma unroll
+        for (int j = 0; j < (1 << s); ++j) pre.w[StepSlots<K, K, 0>::off(i) + j] = tab[(base << s) + j];
+      });
+      loads_issued();
+      ct_step<FAST, K, K, 0, 0, kCtLazy>(x, 0u, base, tabfn, ot, md, pre);
+    } else {
+      ct_step<FAST, K, K, 0, 0, kCtLazy>(x, 0u, base, tabfn, ot, md);
+    }
     if constexpr (FINAL) {
 #pragma unroll
       for (int u = 0; u < R; ++u) x[u] = A::fwd_final(x[u], md);

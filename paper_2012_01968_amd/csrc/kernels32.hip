@@ -470,11 +470,18 @@ static hipError_t launch_col32(const Args32& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// 32 columns where N2 holds no more, and up to 2^21 residues, where the wide tile leaves most CUs without
+// a workgroup.
+// Forward / inverse at 32 and at 8192 / N1 columns, us: 1 vector of 2^13 7.1 / 6.8 and 8.0 / 7.9, 6 of
+// 2^14 7.5 / 7.3 and 8.3 / 8.5, 16 of 2^15 7.5 / 7.3 and 8.6 / 8.6, 16 of 2^17 12.4 / 12.3 and 13.1 / 12.8; but forward and
+// inverse of 90 x 2 of 2^16, inputs from HBM, 98.8 and 96.0.
+constexpr uint64_t kNarrowCols = 1u << 21;
 template <int LOGM, bool INV>
 static hipError_t go_col32(const Args32& a, hipStream_t st) {
   constexpr int wide = col32_wide<LOGM>();
   if constexpr (wide > 32)
-    if ((1u << (a.logN - LOGM)) < (uint32_t)wide) return launch_col32<LOGM, INV, 32>(a, st);
+    if ((1u << (a.logN - LOGM)) < (uint32_t)wide || (a.n_vec << a.logN) <= kNarrowCols)
+      return launch_col32<LOGM, INV, 32>(a, st);
   return launch_col32<LOGM, INV, wide>(a, st);
 }
 

@@ -231,17 +231,26 @@ struct ntt_plan_s {
     a.fast = fast ? 1u : 0u;
     a.mu = d_mu;
     a.bits = d_bits;
-    a.row_lr = row_lr;
-    a.row_nth = row_nth;
     a.col_w = col_w;
     a.debug = debug;
+    row_tile(a);
     return a;
   }
   nttk::Plan32 plan32() const {
     return nttk::Plan32{d_tw32_fwd, d_tw32_inv, d_scale32, d_scale32_mul, d_primes32, L, logN, logN1};
   }
-  // log2 N1 of a launch over n_vec vectors (launch_rules.hpp)
+  // Split and row tile of a launch over n_vec vectors: the library's choice (launch_rules.hpp) for
+  // automatic plans, the plan's for the others, whose options are taken as given.
   uint32_t split_for(uint64_t n_vec) const { return auto_split ? nttr::split(logN, logN1, n_vec, fast) : logN1; }
+  void row_tile(PassArgs& a) const {
+    const bool small = auto_split && nttr::small_rows(logN, a.logN1, a.n_vec);
+    a.row_lr = small ? 2 : row_lr;
+    a.row_nth = small ? 64 : row_nth;
+  }
+  void shape(PassArgs& a) const {
+    a.logN1 = split_for(a.n_vec);
+    row_tile(a);
+  }
   int active_ot() const { return twiddle_mode == NTT_TWIDDLE_OT ? ot_stages : 0; }
   // the paths whose data goes back to global memory after every group of stages
   bool stage_path() const { return kernel_path == NTT_PATH_RADIX2 || kernel_path == NTT_PATH_REGISTER; }
@@ -634,7 +643,7 @@ static hipError_t transform_brv(ntt_plan_t plan, uint64_t* data, uint32_t n_poly
                                 uint32_t limbs) {
   if ((limbs == 0 || limbs == plan->L) && plan->fused_for(n_polys)) return launch_fused(plan, data, n_polys, inverse, st);
   PassArgs a = plan->args(data, n_polys, inverse, limbs);
-  a.logN1 = plan->split_for(a.n_vec);
+  plan->shape(a);
   return enqueue_direction(plan, a, inverse, st);
 }
 
@@ -709,7 +718,8 @@ static hipError_t polymul_enqueue(ntt_plan_t plan, const uint64_t* d_a, const ui
     PassArgs rows = plan->args(d_c, n_polys, false);
     PassArgs inv = plan->args(d_c, n_polys, true);
     inv.scale = plan->d_scale_mul;
-    rows.logN1 = inv.logN1 = plan->split_for(rows.n_vec);
+    plan->shape(rows);
+    plan->shape(inv);
     if (rows.logN1) {
       PassArgs cols = rows;
       cols.src = d_a;
@@ -812,7 +822,7 @@ struct ntt_batch_s {
     a.n_vec = n;
     a.P = 1;
     a.L = g.plan->L;
-    a.logN1 = g.plan->split_for(n);
+    g.plan->shape(a);
     return a;
   }
 

@@ -645,17 +645,11 @@ __global__ __launch_bounds__((ColCfg<LOGM, WREQ>::NT)) void inv_col_kernel(PassA
 constexpr int row_t(int logm, int lr) { return (1 << logm) >> (lr < logm ? lr : logm); }
 constexpr int row_nth_canon(int logm, int lr, int nth) { return row_t(logm, lr) >= nth ? row_t(logm, lr) : nth; }
 
-// Default shape: 8 values per lane and 128 lanes; 4 values and 64 lanes for row passes of at most
-// kSmallRows residues, whose 8-value waves would not fill the SIMDs four deep, so that a wave's own
-// chain of stages is what the launch waits for.  Forward + inverse, us, 8 x 128 / 4 x 64: N = 2^13 x 7
-// vectors 14.5 / 13.1, 2^14 x 48 21.0 / 20.1, 2^16 x 21 34.0 / 32.2; 2^17 x 21 (2.75 M residues)
-// 58.4 / 56.6, 2^15 x 90 (2.95 M) 51.3 / 51.9, 2^16 x 90 94 / 93.5.
-constexpr uint64_t kSmallRows = 1u << 21;
+// Default shape: 8 values per lane and 128 lanes.
 template <int LOGM, typename F>
 __host__ hipError_t with_row_shape(const PassArgs& a, F&& f) {
-  const bool small = LOGM <= 12 && a.logN1 != 0 && !a.row_lr && !a.row_nth && (a.n_vec << a.logN) <= kSmallRows;
-  const int lr = a.row_lr ? (int)a.row_lr : small ? 2 : row_lr(LOGM);
-  const int nth = a.row_nth ? (int)a.row_nth : small ? 64 : kRowThreads;
+  const int lr = a.row_lr ? (int)a.row_lr : row_lr(LOGM);
+  const int nth = a.row_nth ? (int)a.row_nth : kRowThreads;
 #define NTTK_SHAPE(LR_, NTH_)                                                                             \
   if (lr == LR_ && nth == NTH_)                                                                           \
     return f(std::integral_constant<int, row_nth_canon(LOGM, LR_, NTH_)>{}, std::integral_constant<int, LR_>{});

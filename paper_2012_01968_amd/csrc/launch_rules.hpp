@@ -37,4 +37,13 @@ inline uint32_t split(uint32_t log_n, uint32_t log_n1, uint64_t n_vec, bool fast
   return log_n1;
 }
 
+// Whether the row pass of a split launch takes 4 values per lane and 64 lanes instead of 8 and 128: up to
+// 2^21 residues, whose 8-value waves would not fill the SIMDs four deep, so that a wave's own chain of
+// stages is what the launch waits for (rows of up to 2^12 points; a longer one needs more than 1024 lanes).
+// Forward + inverse, us, 8 x 128 / 4 x 64: N = 2^13 x 7 vectors 14.5 / 13.1, 2^14 x 48 21.0 / 20.1, 2^16 x 21
+// 34.0 / 32.2; 2^17 x 21 (2.75 M residues) 58.4 / 56.6, 2^15 x 90 (2.95 M) 51.3 / 51.9, 2^16 x 90 94 / 93.5.
+inline bool small_rows(uint32_t log_n, uint32_t log_n1, uint64_t n_vec) {
+  return log_n1 != 0 && log_n - log_n1 <= 12 && (n_vec << log_n) <= kSmallLaunch;
+}
+
 }  // namespace nttr

@@ -1,5 +1,5 @@
 // Host check of the automatic plans' launch rules (compiled with g++ by the test suite): one pass at
-// N = 2^13 exactly where it measured faster, and the splits on both sides of their lines.
+// N = 2^13 exactly where it measured faster, and the splits and row tiles on both sides of their lines.
 #include <cstdio>
 
 #include "launch_rules.hpp"
@@ -32,6 +32,10 @@ int main() {
     check(nttr::split(15, 6, 64, fast) == 7 && nttr::split(15, 6, 65, fast) == 6, "2^15 at 2^21 residues", 64, fast);
     check(nttr::split(16, 6, 32, fast) == 7 && nttr::split(16, 6, 33, fast) == 6, "2^16 at 2^21 residues", 32, fast);
   }
+  // row tiles: small launches of split sizes only
+  check(nttr::small_rows(13, 5, 256) && !nttr::small_rows(13, 5, 257), "row tile at 2^21 residues", 256, true);
+  check(nttr::small_rows(16, 4, 1) && !nttr::small_rows(17, 4, 1), "row tile of 2^12 and 2^13 points", 1, true);
+  check(!nttr::small_rows(12, 0, 1) && !nttr::small_rows(13, 0, 1), "row tile of one pass", 1, true);
   std::printf("%d failures\n", failures);
   return failures != 0;
 }

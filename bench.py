@@ -22,6 +22,7 @@ CPU oracle timed on this host.  Everything else goes to stderr.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -957,13 +958,19 @@ def serve_bench(args):
            "arena_gib": cfg["capacity_gib"], "lanes": cfg["lanes"]}
     for policy, mode, lanes in (("continuous", ntt.BATCH_GROUPED, cfg["lanes"]), ("per_request", ntt.BATCH_PLAIN, 1)):
         ex = GpuExecutor(plans, keys, cap, lanes=lanes, mode=mode)
-        Server(ex, cap, policy=policy).run(requests(64, 0, 99))             # warm-up
-        st = Server(ex, cap, policy=policy).run(requests(n, args.serve_rate, cfg["seed"]))
+
+        def serve(reqs):
+            # what earlier sections and runs left is collected now: a full collection takes 40-50 ms, half of
+            # the saturated run, and whether one fell due inside it decided its figure
+            gc.collect()
+            return Server(ex, cap, policy=policy).run(reqs)
+
+        serve(requests(64, 0, 99))             # warm-up
+        st = serve(requests(n, args.serve_rate, cfg["seed"]))
         hi = None
         if args.serve_high_rate > 0:
-            hi = Server(ex, cap, policy=policy).run(requests(int(5 * args.serve_high_rate), args.serve_high_rate,
-                                                            cfg["seed"] + 2))
-        sat = Server(ex, cap, policy=policy).run(requests(2000, 0, cfg["seed"] + 1))
+            hi = serve(requests(int(5 * args.serve_high_rate), args.serve_high_rate, cfg["seed"] + 2))
+        sat = serve(requests(2000, 0, cfg["seed"] + 1))
         ex.close()
         out[policy] = {k: (round(v, 4) if isinstance(v, float) else v) for k, v in st.as_dict().items()}
         if hi is not None:

@@ -659,23 +659,28 @@ __host__ hipError_t with_row_shape(const PassArgs& a, F&& f) {
   return hipErrorInvalidValue;
 }
 
+// Workgroups of a row pass: its tiles, rounded up to the eight XCDs (xcd_tile).
+template <typename C>
+uint32_t row_blocks(const PassArgs& a) {
+  return (uint32_t)((((a.n_vec << a.logN1) + C::V - 1) / C::V + 7) / 8 * 8);
+}
+
 template <bool FAST, int LOGM, int OTS, bool ONEP, int NTH, int LRR>
 hipError_t go_fwd_row(const PassArgs& a, hipStream_t st) {
   using C = RowCfg<LOGM, NTH, LRR>;
-  const uint64_t rows = a.n_vec << a.logN1;
-  const uint64_t blocks = ((rows + C::V - 1) / C::V + 7) / 8 * 8;
-  hipLaunchKernelGGL((fwd_row_kernel<FAST, LOGM, OTS, ONEP, NTH, LRR>), dim3((uint32_t)blocks), dim3(C::NT), 0, st, a);
-  return hipGetLastError();
+  return for_vector_parts(a, (uint64_t)C::T << a.logN1, [&](const PassArgs& p) {
+    hipLaunchKernelGGL((fwd_row_kernel<FAST, LOGM, OTS, ONEP, NTH, LRR>), dim3(row_blocks<C>(p)), dim3(C::NT), 0, st, p);
+    return hipGetLastError();
+  });
 }
 
 template <bool FAST, int LOGM, int OTS, bool SCALE0, int NTH, int LRR>
 hipError_t go_inv_row(const PassArgs& a, hipStream_t st) {
   using C = RowCfg<LOGM, NTH, LRR>;
-  const uint64_t rows = a.n_vec << a.logN1;
-  const uint64_t blocks = ((rows + C::V - 1) / C::V + 7) / 8 * 8;
-  hipLaunchKernelGGL((inv_row_kernel<FAST, LOGM, OTS, SCALE0, NTH, LRR>), dim3((uint32_t)blocks), dim3(C::NT), 0, st,
-                     a);
-  return hipGetLastError();
+  return for_vector_parts(a, (uint64_t)C::T << a.logN1, [&](const PassArgs& p) {
+    hipLaunchKernelGGL((inv_row_kernel<FAST, LOGM, OTS, SCALE0, NTH, LRR>), dim3(row_blocks<C>(p)), dim3(C::NT), 0, st, p);
+    return hipGetLastError();
+  });
 }
 
 template <bool FAST, int LOGM, int WREQ>
@@ -818,11 +823,11 @@ hipError_t inv_col(const PassArgs& a, int logm, hipStream_t st) {
 template <bool FAST, int LOGM, int OTS, bool SCALE0, int NTH, int LRR, bool PAIR>
 hipError_t go_mul_row(const PassArgs& af, const PassArgs& ai, hipStream_t st) {
   using C = RowCfg<LOGM, NTH, LRR>;
-  const uint64_t rows = af.n_vec << af.logN1;
-  const uint64_t blocks = ((rows + C::V - 1) / C::V + 7) / 8 * 8;
-  hipLaunchKernelGGL((mul_row_kernel<FAST, LOGM, OTS, SCALE0, NTH, LRR, PAIR>), dim3((uint32_t)blocks), dim3(C::NT), 0,
-                     st, af, ai);
-  return hipGetLastError();
+  return for_vector_parts(af, (uint64_t)C::T << af.logN1, [&](const PassArgs& p) {
+    hipLaunchKernelGGL((mul_row_kernel<FAST, LOGM, OTS, SCALE0, NTH, LRR, PAIR>), dim3(row_blocks<C>(p)), dim3(C::NT),
+                       0, st, p, ai);
+    return hipGetLastError();
+  });
 }
 
 template <bool FAST, int LM, bool PAIR>

@@ -72,6 +72,28 @@ struct PassArgs {
 constexpr uint32_t kDebugPoisonLds = 1;      // poison LDS before use
 constexpr uint32_t kDebugReverseTiles = 2;   // reverse the workgroup -> tile mapping
 
+// go(part) over the vectors of `a`, whole polynomials of dense batches at a time: a launch of 2^32 lanes or
+// more is cut off without an error, so a part has at most 2^31.
+template <typename F>
+inline hipError_t for_vector_parts(const PassArgs& a, uint64_t lanes_per_vec, F&& go) {
+  const uint64_t unit = a.vecs ? 1 : a.L, fit = (1ull << 31) / lanes_per_vec / unit, most = (fit ? fit : 1) * unit;
+  for (uint64_t v = 0; v < a.n_vec; v += most) {
+    PassArgs p = a;
+    p.n_vec = a.n_vec - v < most ? a.n_vec - v : most;
+    if (a.vecs) {
+      p.vecs += v;
+    } else {
+      p.P = (uint32_t)(p.n_vec / unit);
+      p.data += v << a.logN;
+      if (a.src) p.src += v << a.logN;
+      if (a.key) p.key += v << a.logN;
+    }
+    const hipError_t e = go(p);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Base address and limb of vector `vec` of a launch: dense [P][L][N] batches place vector
 // p*L + l at data + (p*L + l)*N with prime l; list launches read both from the list.
 // Residue arrays live in device global memory; addressing them through this type lets

@@ -90,10 +90,10 @@ __global__ __launch_bounds__(kPermThreads) void brv_permute_kernel(PassArgs a) {
 template <int TB>
 static hipError_t go_permute(const PassArgs& a, hipStream_t st) {
   const uint32_t mb = a.logN - 2 * TB;
-  const uint64_t blocks = a.n_vec << mb;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(brv_permute_kernel<TB>, dim3((uint32_t)blocks), dim3(kPermThreads), 0, st, a);
-  return hipGetLastError();
+  return for_vector_parts(a, (uint64_t)kPermThreads << mb, [&](const PassArgs& p) {
+    hipLaunchKernelGGL(brv_permute_kernel<TB>, dim3((uint32_t)(p.n_vec << mb)), dim3(kPermThreads), 0, st, p);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_brv_permute(const PassArgs& a, hipStream_t st) {

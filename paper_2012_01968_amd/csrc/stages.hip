@@ -89,11 +89,13 @@ __global__ __launch_bounds__(kStageThreads) void stage_group_kernel(PassArgs a, 
 
 template <bool FAST, int K, bool INV, bool F1, bool F2, bool F3>
 static hipError_t go_group(const PassArgs& a, uint32_t s0, hipStream_t st) {
-  const uint64_t lanes = a.n_vec << (a.logN - K);
-  const uint64_t blocks = (lanes + kStageThreads - 1) / kStageThreads;
-  hipLaunchKernelGGL((stage_group_kernel<FAST, K, INV, F1, F2, F3>), dim3((uint32_t)blocks), dim3(kStageThreads), 0,
-                     st, a, s0);
-  return hipGetLastError();
+  return for_vector_parts(a, 1ull << (a.logN - K), [&](const PassArgs& p) {
+    const uint64_t lanes = p.n_vec << (a.logN - K);
+    const uint64_t blocks = (lanes + kStageThreads - 1) / kStageThreads;
+    hipLaunchKernelGGL((stage_group_kernel<FAST, K, INV, F1, F2, F3>), dim3((uint32_t)blocks), dim3(kStageThreads), 0,
+                       st, p, s0);
+    return hipGetLastError();
+  });
 }
 
 template <bool FAST, int K>

@@ -1606,13 +1606,13 @@ int32_t ntt_plan_word_bits(ntt_plan_t plan) {
 
 // ---------------------------------------------------------------- RNS <-> integers
 
-static constexpr uint32_t kCrtMaxLimbs = 64;   // reconstruction keeps L words per lane in registers
+static constexpr uint32_t kCrtMaxLimbs = 64;   // a wave of the reconstruction keeps them in registers, half per lane
 
 // Build the conversion tables of a 64-bit plan and upload them (once).
 static ntt_status crt_prepare(ntt_plan_t plan) {
   std::lock_guard<std::mutex> lk(plan->crt.mu);
   if (plan->crt.ready) return NTT_OK;
-  const nttc::CrtTables t = nttc::crt_tables(plan->primes);
+  const nttc::CrtBase t = nttc::crt_base(plan->primes);
   std::vector<nttk::DecomposePrime> dp(t.L);
   std::vector<nttk::ReconstructPrime> rp(t.L);
   bool all_wide = true;

@@ -3,10 +3,8 @@
 // so the host test suite compiles it with g++.
 //
 // For primes q_0 .. q_{L-1} with product Q (W words):
-//   pow2[l][w] = 2^(64 w) mod q_l            (w < kCrtMaxInWords)  integer -> residues
-//   inv[l]     = (Q / q_l)^-1 mod q_l                              residues -> integer
+//   inv[l]     = (Q / q_l)^-1 mod q_l
 //   M[l]       = Q / q_l, W words
-//   kQ[k]      = k * Q, W + 1 words, k = 0 .. L
 // Reconstruction forms x' = sum_l y_l M_l with y_l = r_l inv[l] mod q_l (so x' < L Q and
 // x' = x mod Q) and subtracts the multiple k Q, k = floor(x' / Q).
 //
@@ -57,41 +55,55 @@ inline uint64_t powmod_u128(uint64_t b, uint64_t e, uint64_t q) {
   return r;
 }
 
-struct CrtTables {
+struct CrtBase {
   uint32_t L = 0, W = 0;                 // primes, words of Q
   std::vector<uint64_t> Q;               // W words
-  std::vector<uint64_t> pow2;            // [L][kCrtMaxInWords]
   std::vector<uint64_t> inv;             // [L]
   std::vector<uint64_t> M;               // [L][W]
-  std::vector<uint64_t> kQ;              // [L + 1][W + 1]
 };
 
-inline CrtTables crt_tables(const std::vector<uint64_t>& primes) {
-  CrtTables t;
+inline CrtBase crt_base(const std::vector<uint64_t>& primes) {
+  CrtBase t;
   t.L = (uint32_t)primes.size();
   t.Q = {1};
   for (uint64_t q : primes) mp_mul_small(t.Q, q);
   while (t.Q.size() > 1 && t.Q.back() == 0) t.Q.pop_back();
   t.W = (uint32_t)t.Q.size();
-  t.pow2.assign((size_t)t.L * kCrtMaxInWords, 0);
   t.inv.assign(t.L, 0);
   t.M.assign((size_t)t.L * t.W, 0);
-  t.kQ.assign((size_t)(t.L + 1) * (t.W + 1), 0);
   std::vector<uint64_t> quot;
   for (uint32_t l = 0; l < t.L; ++l) {
     const uint64_t q = primes[l];
-    const uint64_t two64 = (uint64_t)(((u128)1 << 64) % q);
-    uint64_t c = 1 % q;
-    for (uint32_t w = 0; w < kCrtMaxInWords; ++w) {
-      t.pow2[(size_t)l * kCrtMaxInWords + w] = c;
-      c = mulmod_u128(c, two64, q);
-    }
     const uint64_t rem = mp_divmod_small(t.Q, q, quot);
     (void)rem;   // zero: q divides Q
     for (uint32_t w = 0; w < t.W; ++w) t.M[(size_t)l * t.W + w] = quot[w];
     std::vector<uint64_t> tmp;
     const uint64_t m_mod_q = mp_divmod_small(quot, q, tmp);
     t.inv[l] = powmod_u128(m_mod_q, q - 2, q);
+  }
+  return t;
+}
+
+// The same with the word-wise tables of the definitions, which the host check compares it with:
+//   pow2[l][w] = 2^(64 w) mod q_l   (w < kCrtMaxInWords)
+//   kQ[k]      = k * Q, W + 1 words, k = 0 .. L
+struct CrtTables : CrtBase {
+  std::vector<uint64_t> pow2;            // [L][kCrtMaxInWords]
+  std::vector<uint64_t> kQ;              // [L + 1][W + 1]
+};
+
+inline CrtTables crt_tables(const std::vector<uint64_t>& primes) {
+  CrtTables t;
+  static_cast<CrtBase&>(t) = crt_base(primes);
+  t.pow2.assign((size_t)t.L * kCrtMaxInWords, 0);
+  t.kQ.assign((size_t)(t.L + 1) * (t.W + 1), 0);
+  for (uint32_t l = 0; l < t.L; ++l) {
+    const uint64_t q = primes[l], two64 = (uint64_t)(((u128)1 << 64) % q);
+    uint64_t c = 1 % q;
+    for (uint32_t w = 0; w < kCrtMaxInWords; ++w) {
+      t.pow2[(size_t)l * kCrtMaxInWords + w] = c;
+      c = mulmod_u128(c, two64, q);
+    }
   }
   for (uint32_t k = 0; k <= t.L; ++k) {
     std::vector<uint64_t> kq = t.Q;
@@ -130,7 +142,7 @@ inline std::vector<int8_t> signed_digits(const uint64_t* a, size_t words, bool n
 // limb l's slot holds the digits of y_l and slot L the digit k.  [tiles][slices] operand tiles.
 inline uint32_t reconstruct_tiles(uint32_t W) { return W / 4 + 1; }        // 32 columns each, sign included
 inline uint32_t reconstruct_slices(uint32_t L) { return L / 4 + 1; }       // L limbs and k
-inline std::vector<int8_t> digit_matrix_reconstruct(const CrtTables& t) {
+inline std::vector<int8_t> digit_matrix_reconstruct(const CrtBase& t) {
   const uint32_t T = reconstruct_tiles(t.W), S = reconstruct_slices(t.L);
   std::vector<int8_t> f((size_t)T * S * kDigitTile, 0);
   for (uint32_t l = 0; l <= t.L; ++l) {

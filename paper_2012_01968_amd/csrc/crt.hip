@@ -9,8 +9,8 @@
 // sums: at most 513 digit products of at most 2^14, below 2^24.  The tables come from
 // crt_math.hpp (host), laid out as the instruction's operands.
 //
-// A workgroup of four or eight waves takes 128 or 256 coefficients, one column group of 32 per wave (two groups per
-// wave need 172 VGPRs, two waves per SIMD, at 45 primes: decomposition 42 us instead of 38).  The
+// A workgroup of four or eight waves takes 128 or 256 coefficients, 32 per wave (64 per wave need 172 VGPRs,
+// two waves per SIMD, at 45 primes: decomposition 42 us instead of 38).  The
 // coefficients' digits stay in registers for the whole kernel, their loads issued together, and the
 // constant matrix streams through LDS one 32-row tile at a time, loaded while the previous tile
 // is multiplied, so each workgroup reads the matrix (132 KB at 45 primes) once from L2.
@@ -22,8 +22,7 @@ namespace nttk {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kCvtGroups = 1;                        // column groups of 32 coefficients per wave
-constexpr int cvt_coeffs(int nth) { return nth / 64 * 32 * kCvtGroups; }
+constexpr int cvt_coeffs(int nth) { return nth / 64 * 32; }   // coefficients per workgroup
 constexpr uint64_t kDigitBias = 0x8080808080808080ull;
 
 // b * w mod q in [0, 2q) for any b < 2^64, q < 2^62 (Shoup with the exact quotient).
@@ -77,22 +76,14 @@ __device__ __forceinline__ void for_matrix_tiles(const v4i* __restrict__ frag, u
   }
 }
 
-// One tile's products for both column groups: acc[g] = tile (32 rows) x digits of group g.
+// One tile's products: acc = tile (32 rows) x digits of the wave's 32 coefficients.
 template <int KS>
-__device__ __forceinline__ void tile_product(v16i (&acc)[kCvtGroups], const v4i* tile, const v4i (&b)[kCvtGroups][KS],
-                                             uint32_t S, uint32_t lane) {
+__device__ __forceinline__ void tile_product(v16i& acc, const v4i* tile, const v4i (&b)[KS], uint32_t S, uint32_t lane) {
 #pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g)
+  for (int r = 0; r < 16; ++r) acc[r] = 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[g][r] = 0;
-#pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    if ((uint32_t)s < S) {
-      const v4i a = tile[s * 64 + lane];
-#pragma unroll
-      for (int g = 0; g < kCvtGroups; ++g) acc[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[g][s], acc[g], 0, 0, 0);
-    }
-  }
+  for (int s = 0; s < KS; ++s)
+    if ((uint32_t)s < S) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(tile[s * 64 + lane], b[s], acc, 0, 0, 0);
 }
 
 // c0 + 2^8 c1 + 2^16 c2 + 2^24 c3 + add over four int32 columns.
@@ -120,7 +111,7 @@ __global__ __launch_bounds__(256) void rns_decompose_word_kernel(const uint64_t*
 // The bytes enter as signed digits less 128, `offsets` adds the 128s back.  With s = bitlen(q_l),
 // t = floor(V / 2^(s-15)) < 2^32 and mu = floor(2^(s+31) / q_l) < 2^32, the estimate
 // floor(t mu / 2^46) of V / q_l falls short by less than 1 + 2^-13, so V - est q_l < 2 q_l.
-// 2 x 2^16 coefficients at 45 primes of 60 bits: 32 us (2.8 TB/s of words and residues; 132 matrix
+// 2 x 2^16 coefficients at 45 primes of 60 bits: 32 to 34 us by box (2.7 TB/s of words and residues; 132 matrix
 // instructions per 32 coefficients are 7 us of it), against 201 us for one exact Shoup product per
 // word and prime.  Bound by the loads of a wave's digits, which nothing of the same wave overlaps.
 template <int KS, int NTH>
@@ -131,32 +122,26 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
   __shared__ v4i lds[2][KS * 64];
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = (W + 3) / 4;
   const uint64_t N = 1ull << logN;
-  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
-  v4i b[kCvtGroups][KS];
-  uint64_t* out[kCvtGroups];
+  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * 32 + (lane & 31);
+  const uint64_t j = j0 < n_coeffs ? j0 : n_coeffs - 1;   // past the end: read, never stored
+  const uint64_t p = j >> logN, c = j & (N - 1);
+  const uint64_t* x = words + p * W * N + c;
+  uint64_t* out = res + p * L * N + c;
+  v4i b[KS];
 #pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g) {
-    const uint64_t j = j0 + 32 * g < n_coeffs ? j0 + 32 * g : n_coeffs - 1;   // past the end: read, never stored
-    const uint64_t p = j >> logN, c = j & (N - 1);
-    const uint64_t* x = words + p * W * N + c;
-    out[g] = res + p * L * N + c;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const uint32_t w = 4 * s + 2 * h;
-      const uint64_t a0 = w < W ? x[(size_t)w * N] : 0, a1 = w + 1 < W ? x[(size_t)(w + 1) * N] : 0;
-      b[g][s] = digits16(a0, a1);
-    }
+  for (int s = 0; s < KS; ++s) {
+    const uint32_t w = 4 * s + 2 * h;
+    const uint64_t a0 = w < W ? x[(size_t)w * N] : 0, a1 = w + 1 < W ? x[(size_t)(w + 1) * N] : 0;
+    b[s] = digits16(a0, a1);
   }
   loads_issued();
 #pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g)
-#pragma unroll
-    for (int s = 0; s < KS; ++s) b[g][s] ^= (int)0x80808080;
+  for (int s = 0; s < KS; ++s) b[s] ^= (int)0x80808080;
   const uint32_t t0 = blockIdx.y * tiles_per, left = (L + 3) / 4 - t0;   // this workgroup's tiles (decompose_parts)
   for_matrix_tiles<KS, NTH>(frag + (size_t)t0 * stride * 64, stride, left < tiles_per ? left : tiles_per, S, lds,
                             [&](uint32_t t, const v4i* tile) {
     const uint32_t l0 = 4 * (t0 + t) + 2 * h;
-    v16i acc[kCvtGroups];
+    v16i acc;
     tile_product<KS>(acc, tile, b, S, lane);
     static_for<0, 2>([&](auto uc) {
       constexpr int u = decltype(uc)::value;
@@ -164,19 +149,15 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
       if (l < L) {
         const DecomposePrime pr = primes[l];
         const int64_t o0 = offsets[2 * l], o1 = offsets[2 * l + 1];
-#pragma unroll
-        for (int g = 0; g < kCvtGroups; ++g) {
-          const int64_t v0 = columns4<8 * u>(acc[g], o0), v1 = columns4<8 * u + 4>(acc[g], o1);
-          const uint64_t hi = (uint64_t)(v1 + (v0 >> 32));               // V >> 32 (V >= 0)
-          const uint64_t low = (hi << 32) | (uint32_t)v0;                // V mod 2^64
-          uint32_t q15;
-          if (all_wide) q15 = (uint32_t)(hi >> (pr.shift - 32));
-          else if (pr.shift >= 32) q15 = (uint32_t)(hi >> (pr.shift - 32));
-          else q15 = (uint32_t)(pr.shift >= 0 ? low >> pr.shift : low << -pr.shift);   // here V < 2^64
-          const uint32_t k = __umulhi(q15, pr.mu) >> 14;
-          const uint64_t r = csub(low - (uint64_t)k * pr.q, pr.q);
-          if (j0 + 32 * g < n_coeffs) out[g][(size_t)l * N] = r;
-        }
+        const int64_t v0 = columns4<8 * u>(acc, o0), v1 = columns4<8 * u + 4>(acc, o1);
+        const uint64_t hi = (uint64_t)(v1 + (v0 >> 32));               // V >> 32 (V >= 0)
+        const uint64_t low = (hi << 32) | (uint32_t)v0;                // V mod 2^64
+        uint32_t q15;
+        if (all_wide || pr.shift >= 32) q15 = (uint32_t)(hi >> (pr.shift - 32));
+        else q15 = (uint32_t)(pr.shift >= 0 ? low >> pr.shift : low << -pr.shift);   // here V < 2^64
+        const uint32_t k = __umulhi(q15, pr.mu) >> 14;
+        const uint64_t r = csub(low - (uint64_t)k * pr.q, pr.q);
+        if (j0 < n_coeffs) out[(size_t)l * N] = r;
       }
     });
   });
@@ -187,7 +168,7 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
 // units gives k, or k + 1 when x lies within 2^-45 Q of Q; then x - Q < 0 shows in the sign of
 // the result and Q is added back.  Each lane half holds 16 consecutive base-256 columns of a
 // tile, carries them into four 32-bit words and passes its carry on (half 0 to half 1, half 1 to
-// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 37 us, against 576 us for
+// half 0 of the next tile).  2 x 2^16 coefficients at 45 primes of 60 bits: 35 to 38 us by box, against 576 us for
 // 64-bit products with a carry chain per product (93.6 M products of 64 x 64 bits at one wave per
 // SIMD) and a search for k; the same 132 matrix instructions as the decomposition.
 template <int KS, int NTH>
@@ -199,110 +180,87 @@ __global__ __launch_bounds__(NTH) void crt_reconstruct_kernel(
   __shared__ ReconstructPrime pl[4 * KS];   // the primes' constants: a wave meets them one by one
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, S = L / 4 + 1, T = W / 4 + 1;
   const uint64_t N = 1ull << logN;
-  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * (32 * kCvtGroups) + (lane & 31);
-  v4i b[kCvtGroups][KS];
-  uint64_t* o[kCvtGroups];
-  const uint64_t* in[kCvtGroups];
-  uint64_t frac[kCvtGroups];
+  const uint64_t j0 = (uint64_t)blockIdx.x * cvt_coeffs(NTH) + (threadIdx.x >> 6) * 32 + (lane & 31);
+  const uint64_t j = j0 < n_coeffs ? j0 : n_coeffs - 1;   // past the end: read, never stored
+  const uint64_t p = j >> logN, c = j & (N - 1);
+  const uint64_t* in = res + p * L * N + c;
+  uint64_t* o = out + p * W * N + c;
+  uint64_t frac = 0, r[KS][2];
+  v4i b[KS];
 #pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g) {
-    const uint64_t j = j0 + 32 * g < n_coeffs ? j0 + 32 * g : n_coeffs - 1;   // past the end: read, never stored
-    const uint64_t p = j >> logN, c = j & (N - 1);
-    in[g] = res + p * L * N + c;
-    o[g] = out + p * W * N + c;
-    frac[g] = 0;
-  }
-  uint64_t r[kCvtGroups][KS][2];
+  for (int s = 0; s < KS; ++s)
 #pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g)
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const uint32_t l = 4 * s + 2 * h + u;
-        r[g][s][u] = l < L ? in[g][(size_t)l * N] : 0;
-      }
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t l = 4 * s + 2 * h + u;
+      r[s][u] = l < L ? in[(size_t)l * N] : 0;
+    }
   loads_issued();
   if (threadIdx.x < L) pl[threadIdx.x] = primes[threadIdx.x];
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
-    uint64_t y[kCvtGroups][2];
+    uint64_t y[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const uint32_t l = 4 * s + 2 * h + u;
-#pragma unroll
-      for (int g = 0; g < kCvtGroups; ++g) y[g][u] = 0;
+      y[u] = 0;
       if (l < L) {
         const ReconstructPrime pr = pl[l];
         const uint32_t sh = __clzll(pr.q) - 2;
-#pragma unroll
-        for (int g = 0; g < kCvtGroups; ++g) {
-          y[g][u] = csub(shoup_exact(r[g][s][u], pr.inv, pr.inv_b, pr.q), pr.q);
-          frac[g] += __umul64hi(y[g][u] << sh, pr.rec);
-        }
+        y[u] = csub(shoup_exact(r[s][u], pr.inv, pr.inv_b, pr.q), pr.q);
+        frac += __umul64hi(y[u] << sh, pr.rec);
       }
     }
-#pragma unroll
-    for (int g = 0; g < kCvtGroups; ++g)
-      b[g][s] = digits16((y[g][0] + kDigitBias) ^ kDigitBias, (y[g][1] + kDigitBias) ^ kDigitBias);
+    b[s] = digits16((y[0] + kDigitBias) ^ kDigitBias, (y[1] + kDigitBias) ^ kDigitBias);
   }
-#pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g) {
-    const Halves f0 = halves((uint32_t)frac[g]), f1 = halves((uint32_t)(frac[g] >> 32));
+  {
+    const Halves f0 = halves((uint32_t)frac), f1 = halves((uint32_t)(frac >> 32));
     const uint64_t f = make_u64(f0.lo, f1.lo) + make_u64(f0.hi, f1.hi) + 1024;
     const int k = (int)(f >> 56);   // at most L <= 64: one digit
 #pragma unroll
     for (int s = 0; s < KS; ++s)
-      if ((uint32_t)s == L / 4 && (L % 4) / 2 == h) b[g][s][L % 2 ? 2 : 0] = k;
+      if ((uint32_t)s == L / 4 && (L % 4) / 2 == h) b[s][L % 2 ? 2 : 0] = k;
   }
-  uint32_t carry[kCvtGroups] = {};   // out of the previous tile (signed)
-  uint32_t negative[kCvtGroups] = {};
+  uint32_t carry = 0, negative = 0;   // carry: out of the previous tile (signed)
   for_matrix_tiles<KS, NTH>(frag, S, T, S, lds, [&](uint32_t t, const v4i* tile) {
-    v16i acc[kCvtGroups];
+    v16i acc;
     tile_product<KS>(acc, tile, b, S, lane);
-#pragma unroll
-    for (int g = 0; g < kCvtGroups; ++g) {
-      const int64_t t0 = columns4<0>(acc[g], h ? 0 : (int32_t)carry[g]);
-      const int64_t t1 = columns4<4>(acc[g], t0 >> 32);
-      const int64_t t2 = columns4<8>(acc[g], t1 >> 32);
-      const int64_t t3 = columns4<12>(acc[g], t2 >> 32);
-      int32_t over = (int32_t)(t3 >> 32);
-      const uint64_t lo = make_u64((uint32_t)t0, (uint32_t)t1), hi = make_u64((uint32_t)t2, (uint32_t)t3);
-      // half 1 takes half 0's carry: a sign-extended sum over both words and `over`
-      const Halves below = halves((uint32_t)over);   // outside the conditional: both halves take part
-      const int64_t cin = h ? (int32_t)below.lo : 0, sx = cin >> 63;
-      const uint64_t lo2 = lo + (uint64_t)cin, c0 = lo2 < lo;
-      const uint64_t hi1 = hi + (uint64_t)sx, hi2 = hi1 + c0;
-      over += (int32_t)sx + (int32_t)(hi1 < hi) + (int32_t)(hi2 < c0);
-      carry[g] = halves((uint32_t)over).hi;
-      negative[g] = halves((uint32_t)(hi2 >> 32)).hi >> 31;
-      const uint32_t w = 4 * t + 2 * h;
-      if (j0 + 32 * g < n_coeffs) {
-        if (w < W) o[g][(size_t)w * N] = lo2;
-        if (w + 1 < W) o[g][(size_t)(w + 1) * N] = hi2;
-      }
+    const int64_t t0 = columns4<0>(acc, h ? 0 : (int32_t)carry);
+    const int64_t t1 = columns4<4>(acc, t0 >> 32);
+    const int64_t t2 = columns4<8>(acc, t1 >> 32);
+    const int64_t t3 = columns4<12>(acc, t2 >> 32);
+    int32_t over = (int32_t)(t3 >> 32);
+    const uint64_t lo = make_u64((uint32_t)t0, (uint32_t)t1), hi = make_u64((uint32_t)t2, (uint32_t)t3);
+    // half 1 takes half 0's carry: a sign-extended sum over both words and `over`
+    const Halves below = halves((uint32_t)over);   // outside the conditional: both halves take part
+    const int64_t cin = h ? (int32_t)below.lo : 0, sx = cin >> 63;
+    const uint64_t lo2 = lo + (uint64_t)cin, c0 = lo2 < lo;
+    const uint64_t hi1 = hi + (uint64_t)sx, hi2 = hi1 + c0;
+    over += (int32_t)sx + (int32_t)(hi1 < hi) + (int32_t)(hi2 < c0);
+    carry = halves((uint32_t)over).hi;
+    negative = halves((uint32_t)(hi2 >> 32)).hi >> 31;
+    const uint32_t w = 4 * t + 2 * h;
+    if (j0 < n_coeffs) {
+      if (w < W) o[(size_t)w * N] = lo2;
+      if (w + 1 < W) o[(size_t)(w + 1) * N] = hi2;
     }
   });
   // x - Q came out for a lane of the wave: add Q back to the stored words, one lane per coefficient
-#pragma unroll
-  for (int g = 0; g < kCvtGroups; ++g) {
-    const bool fix = negative[g] && j0 + 32 * g < n_coeffs;
-    if (__any(fix)) {
-      __threadfence_block();   // the words that the other half's lanes stored
-      if (fix && h == 0) {
-        uint64_t c = 0;
-        for (uint32_t w = 0; w < W; ++w) {
-          const uint64_t a = o[g][(size_t)w * N], s = a + Q[w], r = s + c;
-          c = (uint64_t)(s < a) | (uint64_t)(r < s);
-          o[g][(size_t)w * N] = r;
-        }
+  const bool fix = negative && j0 < n_coeffs;
+  if (__any(fix)) {
+    __threadfence_block();   // the words that the other half's lanes stored
+    if (fix && h == 0) {
+      uint64_t cy = 0;
+      for (uint32_t w = 0; w < W; ++w) {
+        const uint64_t a = o[(size_t)w * N], s = a + Q[w], r1 = s + cy;
+        cy = (uint64_t)(s < a) | (uint64_t)(r1 < s);
+        o[(size_t)w * N] = r1;
       }
     }
   }
 }
 
-// Slices of a launch rounded up to a built kernel: KS slices of digits stay in registers (8 VGPRs
+// Slices of a launch rounded up to a built kernel: KS slices of digits stay in registers (4 VGPRs
 // each), so a short chain does not pay for a long one's registers.
 #define NTTK_CVT_CASES(X) X(2) X(4) X(8) X(12) X(17)
 

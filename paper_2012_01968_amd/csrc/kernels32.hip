@@ -11,8 +11,9 @@
 // sums (Gentleman-Sande) are brought back into [-q, q) when a stage's outputs would pass 2 q.
 //
 // Measured at N = 2^16, 90 primes, 2 polynomials, forward + inverse: 129 us before (one column per lane,
-// tables of two words, vectorised neither way, rows not grouped by prime), 95 us now: column passes
-// 20-21 us (94 MB), row passes 31 us (118 MB, of them 24 MB of twiddles where 47 MB were).  Between
+// tables of two words, vectorised neither way, rows not grouped by prime), 96 to 101 us now by box.  Under the
+// profiler, which spaces the launches, column passes take 20-21 us (94 MB) and row passes 31 us
+// (118 MB, of them 24 MB of twiddles where 47 MB were).  Between
 // the byte and the instruction bound (16 us): 1.4 rounds of the chip's wave slots leave little
 // overlap between waves.  Product at N = 2^14, 20 primes, 2 polynomials: 44 -> 20 us.
 //

@@ -387,7 +387,8 @@ __global__ __launch_bounds__((RowCfg<LOGM, NTH, LRR>::NT)) void inv_row_kernel(P
 // af carries the data, the second factors and the forward tables; ai the inverse tables and 1/N.
 // SCALE0: single-pass transform (N1 = 1): the whole product happens here.
 
-// Both operands' exchange buffers where they fit 64 KB, else one that they use in turn.
+// Both operands' exchange buffers where they fit 72 KB (two workgroups per CU; rows of 2^12 points take 68),
+// else one that they use in turn.
 template <typename C>
 constexpr bool pair_lds() { return 2 * C::V * C::PITCH * sizeof(uint64_t) <= 72 * 1024; }
 

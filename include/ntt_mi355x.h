@@ -78,13 +78,19 @@ typedef struct {
     int32_t order;          /* NTT_ORDER_*: slot order of the NTT domain (see below)     */
     int32_t log2_radix;     /* NTT_PATH_REGISTER: stages per launch, 2..5; 0 = 4         */
     int32_t word_bits;      /* residue word: 0 or 64 = uint64_t, 32 = uint32_t (below)   */
-    int32_t r1;             /* row pass values per lane (per-thread NTT size): 0 = 8, 4, 8 */
-    int32_t wg_size;        /* row pass workgroup lanes: 0 = 128, 64, 128, 256           */
+    int32_t r1;             /* row pass values per lane (per-thread NTT size): 4, 8; 0 = 8 */
+    int32_t wg_size;        /* row pass workgroup lanes: 64, 128, 256; 0 = 128           */
     int32_t col_width;      /* column pass tile width in adjacent columns: 0 = automatic, */
                             /* 16 .. 256 (at most N2; longer columns take fewer)         */
     int32_t reserved;       /* must be zero                                             */
 } ntt_plan_opts;
-/* Tile options (r1, wg_size, col_width; Section VI-C's per-thread NTT size and thread-block
+/* Automatic plans: a 64-bit plan on the split path that leaves log2_n1 and the tile options at 0
+ * gets its split and row tile per launch, by the vectors of the launch (one pass, other columns,
+ * or 4 values per lane and 64 lanes where that measured faster).  ntt_plan_get_info,
+ * ntt_plan_num_passes and the calls that run single passes describe and use such a plan's default
+ * split.  Plans that name log2_n1, a tile option or another path run as named.
+ *
+ * Tile options (r1, wg_size, col_width; Section VI-C's per-thread NTT size and thread-block
  * shape) apply to 64-bit plans on the split path; elsewhere they are refused with
  * NTT_ERR_UNSUPPORTED, as is r1 = 4 for rows of 8192 points (a row's lanes form one
  * workgroup of at most 1024) and a col_width wider than N2.  The shape applies to every row
@@ -162,7 +168,7 @@ ntt_status ntt_plan_destroy(ntt_plan_t plan);
 /* Copy the L roots psi_l in use into the host array psi_out (L entries). */
 ntt_status ntt_plan_get_roots(ntt_plan_t plan, uint64_t* psi_out);
 
-/* N, L, the pass split, twiddle mode, OT stages and kernel path (NTT_PATH_SPLIT, FUSED,
+/* N, L, the pass split (an automatic plan's default one), twiddle mode, OT stages and kernel path (NTT_PATH_SPLIT, FUSED,
  * RADIX2 or REGISTER; single-pass plans report SPLIT) chosen by the plan.  Any pointer may be
  * NULL. */
 ntt_status ntt_plan_get_info(ntt_plan_t plan, uint32_t* N, uint32_t* L, uint32_t* log2_n1,
@@ -170,7 +176,8 @@ ntt_status ntt_plan_get_info(ntt_plan_t plan, uint32_t* N, uint32_t* L, uint32_t
 
 /* The tile shape the plan was created with (r1, wg_size, col_width of ntt_plan_opts; 0 where
  * the built-in default applies: 8 values per lane and 128-lane row workgroups, or 4 and 64 for
- * small launches, and 64 columns per column tile where N2 holds them, else 16).  Any pointer may be NULL. */
+ * small launches of automatic plans, and 64 columns per column tile where N2 holds them, else
+ * 16).  Any pointer may be NULL. */
 ntt_status ntt_plan_get_tiles(ntt_plan_t plan, int32_t* r1, int32_t* wg_size, int32_t* col_width);
 
 /* In-place forward NTT of every vector of d_data ([n_polys][L][N] uint64, device).
@@ -185,7 +192,7 @@ ntt_status ntt_forward(ntt_plan_t plan, uint64_t* d_data, uint32_t n_polys, void
  * first log2 N1 stages), pass 1 the row pass (the remaining stages, final reduction,
  * bit-reversed output).  A single-pass or fused plan has only pass 0.  A natural-order
  * plan adds the permutation as the last pass.  Running every pass in order equals
- * ntt_forward.  Errors: NTT_ERR_ARG for a pass index at or above ntt_plan_num_passes. */
+ * ntt_forward; between them the data are in the kernels' own form (lazy, below 2^60 signed).  Errors: NTT_ERR_ARG for a pass index at or above ntt_plan_num_passes. */
 ntt_status ntt_forward_pass(ntt_plan_t plan, uint64_t* d_data, uint32_t n_polys, uint32_t pass, void* stream);
 
 /* One kernel of the inverse transform: pass 0 runs the row pass (the first
@@ -195,7 +202,7 @@ ntt_status ntt_forward_pass(ntt_plan_t plan, uint64_t* d_data, uint32_t n_polys,
  * ntt_inverse. */
 ntt_status ntt_inverse_pass(ntt_plan_t plan, uint64_t* d_data, uint32_t n_polys, uint32_t pass, void* stream);
 
-/* Number of kernels per transform for this plan: 1 (single pass or fused) or 2, plus one
+/* Number of passes of ntt_forward_pass / ntt_inverse_pass for this plan: 1 (single pass or fused) or 2, plus one
  * for the permutation of a natural-order plan; 0 for a NULL or destroyed plan. */
 uint32_t ntt_plan_num_passes(ntt_plan_t plan);
 
@@ -311,8 +318,8 @@ ntt_status ntt_batch_destroy(ntt_batch_t batch);
  *
  * The word-size choice of Section IV taken the other way: a plan created with word_bits = 32
  * holds residues in uint32_t words, for primes below 2^30 (four times a prime fits a word,
- * so the lazy butterfly ranges hold), and Montgomery products by one-word multiplicands.  The same modulus budget takes twice the limbs of 64-bit words.  Such a plan
- * takes table twiddles, the split (or single-pass) kernels and bit-reversed order; other
+ * so the lazy butterfly ranges hold), and Montgomery products by one-word multiplicands.  The
+ * same modulus budget takes twice the limbs of 64-bit words.  Such a plan takes table twiddles, the split (or single-pass) kernels and bit-reversed order; other
  * options return NTT_ERR_UNSUPPORTED and primes at or above 2^30 NTT_ERR_PRIME.  Its data
  * goes through the _u32 calls below ([n_polys][L][N] uint32_t, device, 16-byte aligned),
  * with the same meaning, order, streams and errors as their 64-bit counterparts; the other
@@ -334,9 +341,9 @@ int32_t ntt_plan_word_bits(ntt_plan_t plan);
  * Z_Q[X]/(X^N+1), Q = q_0 q_1 ... q_{L-1} (the plan's primes), is held in RNS form as its L
  * residues.  Integers are arrays of little-endian 64-bit words stored word-major:
  * [n_polys][W][N] uint64_t, word w of coefficient c of polynomial p at (p*W + w)*N + c.
- * The first call that needs them builds the conversion tables (Q / q_l, their inverses mod
- * q_l, 2^(64 w) mod q_l, the multiples of Q) and uploads them to the plan's device (a device
- * allocation).  64-bit plans only. */
+ * The first call that needs them builds the conversion tables (the base-256 digits of Q, of Q / q_l and
+ * of 256^j mod q_l, and the inverses of Q / q_l mod q_l) and uploads them to the plan's device (a
+ * device allocation).  64-bit plans only. */
 
 /* Words of Q: the width W of a reconstructed integer.  0 for a NULL, destroyed or 32-bit plan
  * or when the tables cannot be built. */

@@ -491,13 +491,19 @@ static ntt_status build_plan(ntt_plan_s* p, uint32_t N, const uint64_t* primes, 
       };
       Tw* tf = &tw_fwd[l * NN];
       Tw* ti = &tw_inv[l * NN];
-      for (size_t i = 0; i < NN; ++i) {
-        const uint32_t e = nttp::bitrev((uint32_t)i, (int)p->logN);
-        tf[i] = entry(pw[e]);
-        ti[i] = entry(pwi[e]);
-        if (w32) {
-          tw32_f[l * NN + i] = word32(pw[e], q);
-          tw32_i[l * NN + i] = word32(pwi[e], q);
+      for (size_t i0 = 0; i0 < NN; i0 += 8) {   // eight entries at a time: their gathers overlap
+        uint64_t wf[8], wi[8];
+        const size_t n = std::min<size_t>(8, NN - i0);
+        for (size_t k = 0; k < n; ++k) {
+          const uint32_t e = nttp::bitrev((uint32_t)(i0 + k), (int)p->logN);
+          wf[k] = pw[e];
+          wi[k] = pwi[e];
+        }
+        for (size_t k = 0; k < n; ++k) tf[i0 + k] = entry(wf[k]);
+        for (size_t k = 0; k < n; ++k) ti[i0 + k] = entry(wi[k]);
+        for (size_t k = 0; w32 && k < n; ++k) {
+          tw32_f[l * NN + i0 + k] = word32(wf[k], q);
+          tw32_i[l * NN + i0 + k] = word32(wi[k], q);
         }
       }
       for (size_t k = 0; k < B; ++k) {

@@ -11,7 +11,9 @@
 // Both conversions run as products with a constant matrix of base-256 digits (digit_matrix_*
 // below), which the kernels take as int8 matrix-instruction operands.
 #pragma once
+#include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <vector>
 
 namespace nttc {
@@ -124,16 +126,31 @@ inline CrtTables crt_tables(const std::vector<uint64_t>& primes) {
 constexpr uint32_t kDigitTile = 64 * 16;   // bytes of one operand tile
 constexpr uint32_t tile_row(uint32_t m) { return 16 * ((m >> 2) & 1) + (m & 3) + 4 * (m >> 3); }
 
-// Base-256 digits of an integer in [-128, 127], one digit longer than its bytes; with `negate`
-// the digits of its negative (those of the integer then lie in [-127, 128]).
-inline std::vector<int8_t> signed_digits(const uint64_t* a, size_t words, bool negate) {
+// A word's bytes plus kBias are its signed digits plus 128, the carry going on to the next word.
+constexpr uint64_t kBias = 0x8080808080808080ull;
+
+// Base-256 digits of an integer in [-128, 127], one digit longer than its bytes.
+inline std::vector<int8_t> signed_digits(const uint64_t* a, size_t words) {
+  std::vector<int8_t> d(8 * words + 1);
+  u128 sum = 0;
+  for (size_t w = 0; w < words; ++w) {
+    sum = (sum >> 64) + a[w] + kBias;
+    const uint64_t digits = (uint64_t)sum ^ kBias;
+    std::memcpy(&d[8 * w], &digits, 8);
+  }
+  d[8 * words] = (int8_t)(sum >> 64);
+  return d;
+}
+
+// Base-256 digits of the integer's negative, those of the integer then lying in [-127, 128].
+inline std::vector<int8_t> negated_digits(const uint64_t* a, size_t words) {
   std::vector<int8_t> d(8 * words + 1);
   int carry = 0;
   for (size_t i = 0; i < d.size(); ++i) {
     int v = (i < 8 * words ? (int)((a[i / 8] >> (8 * (i % 8))) & 255) : 0) + carry;
-    carry = v > (negate ? 128 : 127);
+    carry = v > 128;
     if (carry) v -= 256;
-    d[i] = (int8_t)(negate ? -v : v);
+    d[i] = (int8_t)-v;
   }
   return d;
 }
@@ -145,17 +162,24 @@ inline uint32_t reconstruct_slices(uint32_t L) { return L / 4 + 1; }       // L 
 inline std::vector<int8_t> digit_matrix_reconstruct(const CrtBase& t) {
   const uint32_t T = reconstruct_tiles(t.W), S = reconstruct_slices(t.L);
   std::vector<int8_t> f((size_t)T * S * kDigitTile, 0);
+  std::vector<int8_t> d(8 + 32 * (size_t)T, 0);   // the digits above seven zeros and more: d[8 + b], b >= -8
   for (uint32_t l = 0; l <= t.L; ++l) {
-    const std::vector<int8_t> d = l < t.L ? signed_digits(&t.M[(size_t)l * t.W], t.W, false)
-                                          : signed_digits(t.Q.data(), t.W, true);
+    const std::vector<int8_t> v = l < t.L ? signed_digits(&t.M[(size_t)l * t.W], t.W) : negated_digits(t.Q.data(), t.W);
+    std::copy(v.begin(), v.end(), d.begin() + 8);   // 8 W + 1 digits, at most 32 T
+    const size_t lane0 = 32 * ((l % 4) / 2), slot = 8 * (l % 2);
     for (uint32_t tile = 0; tile < T; ++tile)
-      for (uint32_t m = 0; m < 32; ++m)
-        for (uint32_t i = 0; i < (l < t.L ? 8u : 1u); ++i) {
-          const int64_t at = (int64_t)32 * tile + tile_row(m) - i;   // column b takes digit b - i of M_l
-          if (at < 0 || at >= (int64_t)d.size()) continue;
-          const uint32_t lane = 32 * ((l % 4) / 2) + m;
-          f[((size_t)tile * S + l / 4) * kDigitTile + lane * 16 + 8 * (l % 2) + i] = d[(size_t)at];
+      for (uint32_t m = 0; m < 32; ++m) {
+        const uint32_t b = 32 * tile + tile_row(m);
+        int8_t* out = &f[((size_t)tile * S + l / 4) * kDigitTile + (lane0 + m) * 16 + slot];
+        if (l == t.L) {
+          *out = d[8 + b];
+        } else {   // column b takes digit b - i of M_l at i = 0 .. 7
+          uint64_t x;
+          std::memcpy(&x, &d[1 + b], 8);
+          x = __builtin_bswap64(x);
+          std::memcpy(out, &x, 8);
         }
+      }
   }
   return f;
 }
@@ -169,9 +193,21 @@ struct DecomposeMatrix {
   std::vector<int8_t> digits;      // [ceil(L / 4)][kDecomposeSlices] operand tiles
   std::vector<int64_t> offsets;    // [kDecomposeSlices + 1][L][2]
 };
+// 8 x 8 bytes: byte i of row j goes to byte j of row i.
+inline void transpose_bytes(uint64_t (&x)[8]) {
+  for (int s = 4; s; s /= 2) {
+    const uint64_t m = s == 4 ? 0x00000000FFFFFFFFull : s == 2 ? 0x0000FFFF0000FFFFull : 0x00FF00FF00FF00FFull;
+    for (int j = 0; j < 8; ++j) {
+      if (j & s) continue;
+      const uint64_t t = ((x[j] >> (8 * s)) ^ x[j + s]) & m;
+      x[j + s] ^= t;
+      x[j] ^= t << (8 * s);
+    }
+  }
+}
+
 inline DecomposeMatrix digit_matrix_decompose(const std::vector<uint64_t>& primes) {
   const uint32_t L = (uint32_t)primes.size(), T = (L + 3) / 4, S = kDecomposeSlices;
-  constexpr uint64_t kBias = 0x8080808080808080ull;
   DecomposeMatrix r;
   r.digits.assign((size_t)T * S * kDigitTile, 0);
   r.offsets.assign((size_t)(S + 1) * L * 2, 0);
@@ -179,22 +215,29 @@ inline DecomposeMatrix digit_matrix_decompose(const std::vector<uint64_t>& prime
   for (uint32_t m = 0; m < 32; ++m) row_of[tile_row(m)] = m;
   for (uint32_t l = 0; l < L; ++l) {
     const uint64_t q = primes[l];
-    const uint64_t b = 256 % q, bb = (uint64_t)(((u128)b << 64) / q);   // Shoup's product by 256
-    uint64_t c = 1 % q;
+    uint64_t k[8], kb[8], c = 1 % q;   // 256^(j + 1) mod q and its companion
+    for (int j = 0; j < 8; ++j) {
+      k[j] = (uint64_t)((u128)(j ? k[j - 1] : 1) * 256 % q);
+      kb[j] = (uint64_t)(((u128)k[j] << 64) / q);
+    }
     int64_t acc[2] = {0, 0};
-    for (uint32_t j = 0; j < 8 * kCrtMaxInWords; ++j) {
-      const uint32_t w = j / 8;
-      const uint64_t d = (c + kBias) ^ kBias;   // c < 2^62: eight signed digits hold it
-      int8_t* tile = &r.digits[((size_t)(l / 4) * S + w / 4) * kDigitTile];
-      for (uint32_t i = 0; i < 8; ++i) {
-        const int8_t di = (int8_t)(d >> (8 * i));
-        tile[(32 * ((w % 4) / 2) + row_of[8 * (l % 4) + i]) * 16 + 8 * (w % 2) + j % 8] = di;
-        acc[i / 4] += (int64_t)di * 128 * ((int64_t)1 << (8 * (i % 4)));
+    for (uint32_t w = 0; w < kCrtMaxInWords; ++w) {   // c = 2^(64 w) mod q
+      uint64_t d[8], next = 0;   // row j: the digits of 256^(8 w + j) mod q, digit i in byte i
+      for (int j = 0; j < 8; ++j) {
+        const uint64_t biased = (j ? next : c) + kBias;   // below 2^62 + kBias: eight signed digits hold it
+        d[j] = biased ^ kBias;
+        acc[0] += 128 * ((int64_t)(uint32_t)biased - 0x80808080);
+        acc[1] += 128 * ((int64_t)(biased >> 32) - 0x80808080);
+        next = c * k[j] - (uint64_t)(((u128)c * kb[j]) >> 64) * q;
+        if (next >= q) next -= q;
       }
-      c = c * b - (uint64_t)(((u128)c * bb) >> 64) * q;
-      if (c >= q) c -= q;
-      if (j % 32 == 31)
-        for (int z = 0; z < 2; ++z) r.offsets[((size_t)(j / 32 + 1) * L + l) * 2 + z] = acc[z];
+      c = next;
+      transpose_bytes(d);   // row i: digit i of the word's eight bytes
+      int8_t* tile = &r.digits[((size_t)(l / 4) * S + w / 4) * kDigitTile];
+      for (uint32_t i = 0; i < 8; ++i)
+        std::memcpy(&tile[(32 * ((w % 4) / 2) + row_of[8 * (l % 4) + i]) * 16 + 8 * (w % 2)], &d[i], 8);
+      if (w % 4 == 3)
+        for (int z = 0; z < 2; ++z) r.offsets[((size_t)(w / 4 + 1) * L + l) * 2 + z] = acc[z];
     }
   }
   return r;

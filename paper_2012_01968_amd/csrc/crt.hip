@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void rns_decompose_word_kernel(const uint64_t*
 // 2 x 2^16 coefficients at 45 primes of 60 bits: 32 to 34 us by box (2.7 TB/s of words and residues; 132 matrix
 // instructions per 32 coefficients are 7 us of it), against 201 us for one exact Shoup product per
 // word and prime.  Bound by the loads of a wave's digits, which nothing of the same wave overlaps.
-template <int KS, int NTH>
+template <int KS, int NTH, bool PARTS>
 __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
     const uint64_t* __restrict__ words, uint32_t W, uint64_t* __restrict__ res, uint64_t n_coeffs, uint32_t logN,
     uint32_t L, const v4i* __restrict__ frag, uint32_t stride, const DecomposePrime* __restrict__ primes,
@@ -137,9 +137,10 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
   loads_issued();
 #pragma unroll
   for (int s = 0; s < KS; ++s) b[s] ^= (int)0x80808080;
-  const uint32_t t0 = blockIdx.y * tiles_per, left = (L + 3) / 4 - t0;   // this workgroup's tiles (decompose_parts)
-  for_matrix_tiles<KS, NTH>(frag + (size_t)t0 * stride * 64, stride, left < tiles_per ? left : tiles_per, S, lds,
-                            [&](uint32_t t, const v4i* tile) {
+  // the tiles of this workgroup (decompose_parts)
+  const uint32_t T = (L + 3) / 4, t0 = PARTS ? blockIdx.y * tiles_per : 0;
+  const uint32_t tiles = PARTS && T - t0 > tiles_per ? tiles_per : T - t0;
+  for_matrix_tiles<KS, NTH>(frag + (size_t)t0 * stride * 64, stride, tiles, S, lds, [&](uint32_t t, const v4i* tile) {
     const uint32_t l0 = 4 * (t0 + t) + 2 * h;
     v16i acc;
     tile_product<KS>(acc, tile, b, S, lane);
@@ -152,8 +153,10 @@ __global__ __launch_bounds__(NTH) void rns_decompose_kernel(
         const int64_t v0 = columns4<8 * u>(acc, o0), v1 = columns4<8 * u + 4>(acc, o1);
         const uint64_t hi = (uint64_t)(v1 + (v0 >> 32));               // V >> 32 (V >= 0)
         const uint64_t low = (hi << 32) | (uint32_t)v0;                // V mod 2^64
+        const int32_t high_shift = pr.shift - 32;
         uint32_t q15;
-        if (all_wide || pr.shift >= 32) q15 = (uint32_t)(hi >> (pr.shift - 32));
+        if (all_wide) q15 = (uint32_t)(hi >> high_shift);
+        else if (pr.shift >= 32) q15 = (uint32_t)(hi >> high_shift);
         else q15 = (uint32_t)(pr.shift >= 0 ? low >> pr.shift : low << -pr.shift);   // here V < 2^64
         const uint32_t k = __umulhi(q15, pr.mu) >> 14;
         const uint64_t r = csub(low - (uint64_t)k * pr.q, pr.q);
@@ -304,13 +307,14 @@ hipError_t launch_rns_decompose(const uint64_t* words, uint32_t W, uint64_t* res
   return with_cvt_threads(n, [&](auto nth) {
     constexpr int NTH = decltype(nth)::value;
     const uint32_t blocks = cvt_blocks(n, NTH), parts = decompose_parts(blocks, T, S), per = (T + parts - 1) / parts;
-#define X(KS)                                                                                                      \
-    if (S <= KS) {                                                                                                 \
-      hipLaunchKernelGGL((rns_decompose_kernel<KS, NTH>), dim3(blocks, (T + per - 1) / per), dim3(NTH), 0, st,     \
-                         words, W, res, n, logN, L, static_cast<const v4i*>(frag), frag_slices, primes,            \
-                         offsets + (size_t)S * L * 2, (uint32_t)all_wide, per);                                    \
-      return hipGetLastError();                                                                                    \
-    }
+    const dim3 grid(blocks, (T + per - 1) / per);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(NTH), 0, st, words, W, res, n, logN, L, static_cast<const v4i*>(frag),
+                         frag_slices, primes, offsets + (size_t)S * L * 2, (uint32_t)all_wide, per);
+      return hipGetLastError();
+    };
+#define X(KS) \
+    if (S <= KS) return per < T ? launch(rns_decompose_kernel<KS, NTH, true>) : launch(rns_decompose_kernel<KS, NTH, false>);
     NTTK_CVT_CASES(X)
 #undef X
     return hipErrorInvalidValue;
